@@ -15,6 +15,7 @@ constexpr float kNegInf = -__builtin_huge_valf();
 struct Bf16 {
   using storage = uint16_t;
   static constexpr int kVec = 8;
+  static __device__ __forceinline__ storage neg_inf() { return 0xff80u; }
   static __device__ __forceinline__ void unpack(const uint4& w, float (&x)[8]) {
     x[0] = __builtin_bit_cast(float, w.x << 16);
     x[1] = __builtin_bit_cast(float, w.x & 0xffff0000u);
@@ -34,6 +35,7 @@ struct Bf16 {
 struct F32 {
   using storage = float;
   static constexpr int kVec = 4;
+  static __device__ __forceinline__ storage neg_inf() { return kNegInf; }
   static __device__ __forceinline__ void unpack(const uint4& w, float (&x)[4]) {
     x[0] = __builtin_bit_cast(float, w.x);
     x[1] = __builtin_bit_cast(float, w.y);

@@ -29,38 +29,36 @@ constexpr int kBlock = kRowBlock;
 constexpr int kWaves = kRowWaves;
 constexpr float kLn2 = 0.693147180559945309417f;
 
-template <class TI, bool VEC, int U, bool NEED_T>
-__global__ __launch_bounds__(kBlock) void k_gen_rows(const void* __restrict__ zd, const void* __restrict__ zt,
+template <class TI, bool VEC, int U, bool NEED_T, int BLK>
+__global__ __launch_bounds__(BLK) void k_gen_rows(const void* __restrict__ zd, const void* __restrict__ zt,
                                                      const int32_t* __restrict__ labels, int V, float scd,
                                                      float sct, int want_eal, int want_pq, int want_kl,
                                                      GenStats* __restrict__ stats) {
-  using Gr = Groups<TI, VEC>;
-  constexpr int E = Gr::E;
-  __shared__ LseState sh_lse[kWaves];
-  __shared__ float sh_f[kWaves];
-  __shared__ int sh_i[kWaves];
+  using Rv = RowVecs<TI, VEC>;
+  constexpr int E = Rv::E;
+  __shared__ LseState sh_lse[BLK / kWave];
+  __shared__ float sh_f[BLK / kWave];
+  __shared__ int sh_i[BLK / kWave];
 
   const int64_t row = blockIdx.x;
-  const int ng = V / E;
-  const int64_t g0 = row * int64_t(ng);
+  const Rv rv(row, gridDim.x, V);
   const int64_t e0 = row * int64_t(V);
   const bool argmax = NEED_T && want_eal && labels == nullptr;
 
   LseState sd = lse_init(), st = lse_init();
   float best = kNegInf;
   int bidx = INT_MAX;
-  for (int base = threadIdx.x; base < ng; base += kBlock * U) {
+  for (int base = threadIdx.x; base < rv.ng; base += BLK * U) {
     float xd[U][E], xt[U][E];
-#pragma unroll
-    for (int u = 0; u < U; ++u) {
-      const int gi = base + u * kBlock;
-      if (gi < ng) {
-        Gr::load(zd, g0, gi, xd[u]);
-        if constexpr (NEED_T) Gr::load(zt, g0, gi, xt[u]);
-      } else {
-#pragma unroll
-        for (int e = 0; e < E; ++e) xd[u][e] = xt[u][e] = kNegInf;
-      }
+    if constexpr (NEED_T) {
+      u32x4 w[2][U];
+      rv.load({zd, zt}, base, BLK, w);
+      rv.unpack(w[0], xd);
+      rv.unpack(w[1], xt);
+    } else {
+      u32x4 w[1][U];
+      rv.load({zd}, base, BLK, w);
+      rv.unpack(w[0], xd);
     }
     float cm = kNegInf;
 #pragma unroll
@@ -98,13 +96,13 @@ __global__ __launch_bounds__(kBlock) void k_gen_rows(const void* __restrict__ zd
           for (int e = 0; e < E; ++e)
             if (xt[u][e] > best) {
               best = xt[u][e];
-              bidx = (base + u * kBlock) * E + e;
+              bidx = rv.index(base + u * BLK, e);
             }
       }
     }
   }
 
-  sd = block_lse(sd, scd, sh_lse);
+  sd = block_lse<BLK / kWave>(sd, scd, sh_lse);
   const float l2sd = __log2f(sd.s);
   GenStats out{};
   out.msc_d = sd.msc;
@@ -115,7 +113,7 @@ __global__ __launch_bounds__(kBlock) void k_gen_rows(const void* __restrict__ zd
     if (labels != nullptr) {
       x = min(max(labels[row], 0), V - 1);  // out-of-range labels are clamped
     } else {
-      x = block_argmax(best, bidx, sh_f, sh_i);
+      x = block_argmax<BLK / kWave>(best, bidx, sh_f, sh_i);
       if (x == INT_MAX) x = 0;  // no finite target logit: unspecified, stay in bounds
     }
     const float zx = TI::load1(zd, e0 + x);
@@ -123,22 +121,15 @@ __global__ __launch_bounds__(kBlock) void k_gen_rows(const void* __restrict__ zd
     out.xstar = x;
   }
   if (NEED_T && want_pq) {
-    st = block_lse(st, sct, sh_lse);
+    st = block_lse<BLK / kWave>(st, sct, sh_lse);
     const float l2st = __log2f(st.s);
     float smin = 0.f, qlt = 0.f, kl = 0.f;
-    for (int base = threadIdx.x; base < ng; base += kBlock * U) {
+    for (int base = threadIdx.x; base < rv.ng; base += BLK * U) {
+      u32x4 w[2][U];
       float xd[U][E], xt[U][E];
-#pragma unroll
-      for (int u = 0; u < U; ++u) {
-        const int gi = base + u * kBlock;
-        if (gi < ng) {
-          Gr::load(zd, g0, gi, xd[u]);
-          Gr::load(zt, g0, gi, xt[u]);
-        } else {
-#pragma unroll
-          for (int e = 0; e < E; ++e) xd[u][e] = xt[u][e] = kNegInf;
-        }
-      }
+      rv.load({zd, zt}, base, BLK, w);
+      rv.unpack(w[0], xd);
+      rv.unpack(w[1], xt);
       float am = 0.f, aq = 0.f, ak = 0.f;
 #pragma unroll
       for (int u = 0; u < U; ++u)
@@ -158,9 +149,9 @@ __global__ __launch_bounds__(kBlock) void k_gen_rows(const void* __restrict__ zd
       qlt += aq;
       kl += ak;
     }
-    smin = block_sum(smin, sh_f);
-    qlt = block_sum(qlt, sh_f);
-    if (want_kl) kl = block_sum(kl, sh_f);
+    smin = block_sum<BLK / kWave>(smin, sh_f);
+    qlt = block_sum<BLK / kWave>(qlt, sh_f);
+    if (want_kl) kl = block_sum<BLK / kWave>(kl, sh_f);
     out.a_tv = smin;
     out.qlt = qlt;
     out.kl = kl * kLn2;
@@ -339,22 +330,27 @@ template <class TI, class TG, bool VEC, int U, bool NEED_P>
 __global__ __launch_bounds__(kBlock) void k_gen_grad(const void* __restrict__ zd, const void* __restrict__ zt, int V,
                                                      float scd, float sct, const GenStats* __restrict__ stats,
                                                      void* __restrict__ grad) {
-  using Gr = Groups<TI, VEC>;
-  constexpr int E = Gr::E;
+  using Rv = RowVecs<TI, VEC>;
+  constexpr int E = Rv::E;
+  constexpr int NT = NEED_P ? 2 : 1;
   const int64_t row = blockIdx.x;
-  const int ng = V / E;
-  const int64_t g0 = row * int64_t(ng);
+  const Rv rv(row, gridDim.x, V);
   const GenStats s = stats[row];
-  for (int base = threadIdx.x; base < ng; base += kBlock * U) {
+  for (int base = blockIdx.y * kBlock * U + threadIdx.x; base < rv.ng; base += gridDim.y * kBlock * U) {
+    u32x4 w[NT][U];
+    if constexpr (NEED_P)
+      rv.load({zd, zt}, base, kBlock, w);
+    else
+      rv.load({zd}, base, kBlock, w);
 #pragma unroll
     for (int u = 0; u < U; ++u) {
       const int gi = base + u * kBlock;
-      if (gi >= ng) break;
+      if (gi >= rv.ng) break;
       float xd[E], g[E];
-      Gr::load(zd, g0, gi, xd);
+      TI::unpack(to_uint4(w[0][u]), xd);
       if constexpr (NEED_P) {
         float xt[E];
-        Gr::load(zt, g0, gi, xt);
+        TI::unpack(to_uint4(w[NT - 1][u]), xt);
 #pragma unroll
         for (int e = 0; e < E; ++e) {
           const float ld = __builtin_fmaf(xd[e], scd, -s.msc_d) - s.l2s_d;
@@ -367,46 +363,45 @@ __global__ __launch_bounds__(kBlock) void k_gen_grad(const void* __restrict__ zd
       }
 #pragma unroll
       for (int e = 0; e < E; ++e)
-        if (gi * E + e == s.xstar) g[e] += s.cX;
-      if constexpr (VEC) {
-        store_vec<TG, E>(grad, (g0 + gi) * E, g);
-      } else {
-        TG::store1(grad, g0 + gi, g[0]);
-      }
+        if (rv.index(gi, e) == s.xstar) g[e] += s.cX;
+      rv.template store<TG>(grad, gi, g);
     }
   }
 }
 
-template <class TI, bool VEC, int U, bool NEED_T>
-void rows_launch(const GenArgs& a, const GenStats* unused) {
-  (void)unused;
-  k_gen_rows<TI, VEC, U, NEED_T><<<dim3(unsigned(a.R)), kBlock, 0, a.stream>>>(
+template <class TI, bool VEC, bool NEED_T, int BLK>
+void rows_blk(const GenArgs& a) {
+  k_gen_rows<TI, VEC, 4, NEED_T, BLK><<<dim3(unsigned(a.R)), BLK, 0, a.stream>>>(
       a.zd, a.zt, a.labels, a.V, a.sc_d, a.sc_t, a.w_eal != 0.f, a.w_wtv != 0.f || a.w_tv != 0.f || a.w_kl != 0.f,
       a.w_kl != 0.f, a.stats);
 }
 
-template <class TI, class TG, bool VEC, int U>
-void grad_launch(const GenArgs& a, bool need_p) {
-  if (need_p)
-    k_gen_grad<TI, TG, VEC, U, true><<<dim3(unsigned(a.R)), kBlock, 0, a.stream>>>(a.zd, a.zt, a.V, a.sc_d, a.sc_t,
-                                                                                  a.stats, a.grad);
+template <class TI, bool VEC, bool NEED_T>
+void rows_launch(const GenArgs& a) {
+  if (wide_rows(a.R, a.V))
+    rows_blk<TI, VEC, NEED_T, kWideBlock>(a);
   else
-    k_gen_grad<TI, TG, VEC, U, false><<<dim3(unsigned(a.R)), kBlock, 0, a.stream>>>(a.zd, a.zt, a.V, a.sc_d, a.sc_t,
-                                                                                   a.stats, a.grad);
+    rows_blk<TI, VEC, NEED_T, kBlock>(a);
 }
 
-template <class TI>
-hipError_t launch_typed(const GenArgs& a) {
-  const bool vec = (a.V % TI::kVec) == 0;
+template <class TI, class TG, bool VEC>
+void grad_launch(const GenArgs& a, bool need_p) {
+  constexpr int U = 4;
+  const dim3 grid(unsigned(a.R), row_splits(a.R, a.V, TI::kVec, U));
+  if (need_p)
+    k_gen_grad<TI, TG, VEC, U, true><<<grid, kBlock, 0, a.stream>>>(a.zd, a.zt, a.V, a.sc_d, a.sc_t, a.stats, a.grad);
+  else
+    k_gen_grad<TI, TG, VEC, U, false><<<grid, kBlock, 0, a.stream>>>(a.zd, a.zt, a.V, a.sc_d, a.sc_t, a.stats, a.grad);
+}
+
+template <class TI, bool VEC>
+hipError_t launch_vec(const GenArgs& a) {
   const bool need_pq = a.w_wtv != 0.f || a.w_tv != 0.f || a.w_kl != 0.f;
   const bool need_t = need_pq || (a.w_eal != 0.f && a.labels == nullptr);
-  if (vec) {
-    if (need_t) rows_launch<TI, true, 4, true>(a, nullptr);
-    else rows_launch<TI, true, 4, false>(a, nullptr);
-  } else {
-    if (need_t) rows_launch<TI, false, 8, true>(a, nullptr);
-    else rows_launch<TI, false, 8, false>(a, nullptr);
-  }
+  if (need_t)
+    rows_launch<TI, VEC, true>(a);
+  else
+    rows_launch<TI, VEC, false>(a);
   ScanParams sp{};
   sp.stats = a.stats;
   sp.layout = a.layout;
@@ -431,15 +426,17 @@ hipError_t launch_typed(const GenArgs& a) {
   k_gen_scan<<<dim3(unsigned((a.R + kBlock - 1) / kBlock)), kBlock, 0, a.stream>>>(sp);
   if (hipError_t e = launch_general_loss(a); e != hipSuccess) return e;
   if (a.grad) {
-    if (a.gd == DType::kBf16) {
-      if (vec) grad_launch<TI, GBf16, true, 4>(a, need_pq);
-      else grad_launch<TI, GBf16, false, 8>(a, need_pq);
-    } else {
-      if (vec) grad_launch<TI, GF32, true, 4>(a, need_pq);
-      else grad_launch<TI, GF32, false, 8>(a, need_pq);
-    }
+    if (a.gd == DType::kBf16)
+      grad_launch<TI, GBf16, VEC>(a, need_pq);
+    else
+      grad_launch<TI, GF32, VEC>(a, need_pq);
   }
   return hipGetLastError();
+}
+
+template <class TI>
+hipError_t launch_typed(const GenArgs& a) {
+  return a.V % TI::kVec == 0 ? launch_vec<TI, true>(a) : launch_vec<TI, false>(a);
 }
 
 }  // namespace

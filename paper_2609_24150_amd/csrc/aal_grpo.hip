@@ -29,37 +29,36 @@ constexpr int kBlock = kRowBlock;
 constexpr int kWaves = kRowWaves;
 constexpr float kLn2 = 0.693147180559945309417f;
 
-template <class TI, bool VEC, int U, bool TARGET>
-__global__ __launch_bounds__(kBlock) void k_grpo_rows(const void* __restrict__ zth, const void* __restrict__ zrf,
+template <class TI, bool VEC, int U, bool TARGET, int BLK>
+__global__ __launch_bounds__(BLK) void k_grpo_rows(const void* __restrict__ zth, const void* __restrict__ zrf,
                                                       const void* __restrict__ zt, const int32_t* __restrict__ labels,
                                                       int V, float sc, GrpoRow* __restrict__ rows) {
-  using Gr = Groups<TI, VEC>;
-  constexpr int E = Gr::E;
-  __shared__ LseState sh_lse[kWaves];
-  __shared__ float sh_f[kWaves];
-  __shared__ int sh_i[kWaves];
+  using Rv = RowVecs<TI, VEC>;
+  constexpr int E = Rv::E;
+  __shared__ LseState sh_lse[BLK / kWave];
+  __shared__ float sh_f[BLK / kWave];
+  __shared__ int sh_i[BLK / kWave];
 
   const int64_t row = blockIdx.x;
-  const int ng = V / E;
-  const int64_t g0 = row * int64_t(ng);
+  const Rv rv(row, gridDim.x, V);
   const int64_t e0 = row * int64_t(V);
 
   LseState sth = lse_init(), srf = lse_init();
   float bth = kNegInf, brf = kNegInf, bt = kNegInf;
   int ith = INT_MAX, irf = INT_MAX, it = INT_MAX;
-  for (int base = threadIdx.x; base < ng; base += kBlock * U) {
+  for (int base = threadIdx.x; base < rv.ng; base += BLK * U) {
     float xa[U][E], xb[U][E], xc[U][E];
-#pragma unroll
-    for (int u = 0; u < U; ++u) {
-      const int gi = base + u * kBlock;
-      if (gi < ng) {
-        Gr::load(zth, g0, gi, xa[u]);
-        Gr::load(zrf, g0, gi, xb[u]);
-        if constexpr (TARGET) Gr::load(zt, g0, gi, xc[u]);
-      } else {
-#pragma unroll
-        for (int e = 0; e < E; ++e) xa[u][e] = xb[u][e] = xc[u][e] = kNegInf;
-      }
+    if constexpr (TARGET) {
+      u32x4 w[3][U];
+      rv.load({zth, zrf, zt}, base, BLK, w);
+      rv.unpack(w[0], xa);
+      rv.unpack(w[1], xb);
+      rv.unpack(w[2], xc);
+    } else {
+      u32x4 w[2][U];
+      rv.load({zth, zrf}, base, BLK, w);
+      rv.unpack(w[0], xa);
+      rv.unpack(w[1], xb);
     }
     float ca = kNegInf, cb = kNegInf;
 #pragma unroll
@@ -68,7 +67,7 @@ __global__ __launch_bounds__(kBlock) void k_grpo_rows(const void* __restrict__ z
       for (int e = 0; e < E; ++e) {
         ca = fmaxf(ca, xa[u][e]);
         cb = fmaxf(cb, xb[u][e]);
-        const int idx = (base + u * kBlock) * E + e;
+        const int idx = rv.index(base + u * BLK, e);
         if (xa[u][e] > bth) { bth = xa[u][e]; ith = idx; }
         if (xb[u][e] > brf) { brf = xb[u][e]; irf = idx; }
         if constexpr (TARGET) {
@@ -92,13 +91,13 @@ __global__ __launch_bounds__(kBlock) void k_grpo_rows(const void* __restrict__ z
       srf.s += acc;
     }
   }
-  sth = block_lse(sth, sc, sh_lse);
-  srf = block_lse(srf, sc, sh_lse);
-  int s_th = block_argmax(bth, ith, sh_f, sh_i);
-  int s_rf = block_argmax(brf, irf, sh_f, sh_i);
+  sth = block_lse<BLK / kWave>(sth, sc, sh_lse);
+  srf = block_lse<BLK / kWave>(srf, sc, sh_lse);
+  int s_th = block_argmax<BLK / kWave>(bth, ith, sh_f, sh_i);
+  int s_rf = block_argmax<BLK / kWave>(brf, irf, sh_f, sh_i);
   int xs;
   if constexpr (TARGET) {
-    xs = block_argmax(bt, it, sh_f, sh_i);
+    xs = block_argmax<BLK / kWave>(bt, it, sh_f, sh_i);
     if (xs == INT_MAX) xs = 0;
   } else {
     xs = min(max(labels[row], 0), V - 1);  // out-of-range labels are clamped
@@ -179,8 +178,8 @@ template <class TI, class TG, bool VEC, int U>
 __global__ __launch_bounds__(kBlock) void k_grpo_grad(const void* __restrict__ zth, int V, float sc, float inv_t,
                                                       const float* __restrict__ grad_scale, GroupParams p,
                                                       void* __restrict__ grad) {
-  using Gr = Groups<TI, VEC>;
-  constexpr int E = Gr::E;
+  using Rv = RowVecs<TI, VEC>;
+  constexpr int E = Rv::E;
   __shared__ float sh_c;
   const int64_t row = blockIdx.x;
   const GrpoRow s = p.rows[row];
@@ -205,47 +204,48 @@ __global__ __launch_bounds__(kBlock) void k_grpo_grad(const void* __restrict__ z
   }
   __syncthreads();
   const float c = sh_c;
-  const int ng = V / E;
-  const int64_t g0 = row * int64_t(ng);
-  for (int base = threadIdx.x; base < ng; base += kBlock * U) {
+  const Rv rv(row, gridDim.x, V);
+  for (int base = blockIdx.y * kBlock * U + threadIdx.x; base < rv.ng; base += gridDim.y * kBlock * U) {
+    u32x4 w[1][U];
+    rv.load({zth}, base, kBlock, w);
 #pragma unroll
     for (int u = 0; u < U; ++u) {
       const int gi = base + u * kBlock;
-      if (gi >= ng) break;
+      if (gi >= rv.ng) break;
       float x[E], g[E];
-      Gr::load(zth, g0, gi, x);
+      TI::unpack(to_uint4(w[0][u]), x);
 #pragma unroll
       for (int e = 0; e < E; ++e) {
         const float pv = ex2(__builtin_fmaf(x[e], sc, -s.msc) - s.l2s);
-        g[e] = c * (((gi * E + e) == s.s_theta ? 1.f : 0.f) - pv);
+        g[e] = c * ((rv.index(gi, e) == s.s_theta ? 1.f : 0.f) - pv);
       }
-      if constexpr (VEC) {
-        store_vec<TG, E>(grad, (g0 + gi) * E, g);
-      } else {
-        TG::store1(grad, g0 + gi, g[0]);
-      }
+      rv.template store<TG>(grad, gi, g);
     }
   }
 }
 
-template <class TI, class TG, bool VEC, int U>
-void grad_launch(const GrpoArgs& a, const GroupParams& gp) {
-  k_grpo_grad<TI, TG, VEC, U><<<dim3(unsigned(a.R)), kBlock, 0, a.stream>>>(a.zth, a.V, a.sc, a.inv_t,
-                                                                           a.grad_scale, gp, a.grad);
+template <class TI, bool VEC, int BLK>
+void rows_launch(const GrpoArgs& a) {
+  const unsigned R = unsigned(a.R);
+  if (a.labels == nullptr)
+    k_grpo_rows<TI, VEC, 2, true, BLK><<<R, BLK, 0, a.stream>>>(a.zth, a.zrf, a.zt, a.labels, a.V, a.sc, a.rows);
+  else
+    k_grpo_rows<TI, VEC, 2, false, BLK><<<R, BLK, 0, a.stream>>>(a.zth, a.zrf, a.zt, a.labels, a.V, a.sc, a.rows);
 }
 
-template <class TI>
-hipError_t launch_typed(const GrpoArgs& a) {
-  const bool vec = (a.V % TI::kVec) == 0;
-  const bool tgt = a.labels == nullptr;
-  const unsigned R = unsigned(a.R);
-  if (vec) {
-    if (tgt) k_grpo_rows<TI, true, 2, true><<<R, kBlock, 0, a.stream>>>(a.zth, a.zrf, a.zt, a.labels, a.V, a.sc, a.rows);
-    else k_grpo_rows<TI, true, 2, false><<<R, kBlock, 0, a.stream>>>(a.zth, a.zrf, a.zt, a.labels, a.V, a.sc, a.rows);
-  } else {
-    if (tgt) k_grpo_rows<TI, false, 4, true><<<R, kBlock, 0, a.stream>>>(a.zth, a.zrf, a.zt, a.labels, a.V, a.sc, a.rows);
-    else k_grpo_rows<TI, false, 4, false><<<R, kBlock, 0, a.stream>>>(a.zth, a.zrf, a.zt, a.labels, a.V, a.sc, a.rows);
-  }
+template <class TI, class TG, bool VEC>
+void grad_launch(const GrpoArgs& a, const GroupParams& gp) {
+  constexpr int U = 4;
+  k_grpo_grad<TI, TG, VEC, U><<<dim3(unsigned(a.R), row_splits(a.R, a.V, TI::kVec, U)), kBlock, 0, a.stream>>>(
+      a.zth, a.V, a.sc, a.inv_t, a.grad_scale, gp, a.grad);
+}
+
+template <class TI, bool VEC>
+hipError_t launch_vec(const GrpoArgs& a) {
+  if (wide_rows(a.R, a.V))
+    rows_launch<TI, VEC, kWideBlock>(a);
+  else
+    rows_launch<TI, VEC, kBlock>(a);
   GroupParams gp{};
   gp.rows = a.rows;
   gp.layout = a.layout;
@@ -269,15 +269,17 @@ hipError_t launch_typed(const GrpoArgs& a) {
   k_grpo_groups<<<dim3(unsigned((a.n_groups + kBlock - 1) / kBlock)), kBlock, 0, a.stream>>>(gp);
   k_grpo_loss<<<1, kBlock, 0, a.stream>>>(a.group_loss, a.n_groups, a.loss);
   if (a.grad) {
-    if (a.gd == DType::kBf16) {
-      if (vec) grad_launch<TI, GBf16, true, 4>(a, gp);
-      else grad_launch<TI, GBf16, false, 8>(a, gp);
-    } else {
-      if (vec) grad_launch<TI, GF32, true, 4>(a, gp);
-      else grad_launch<TI, GF32, false, 8>(a, gp);
-    }
+    if (a.gd == DType::kBf16)
+      grad_launch<TI, GBf16, VEC>(a, gp);
+    else
+      grad_launch<TI, GF32, VEC>(a, gp);
   }
   return hipGetLastError();
+}
+
+template <class TI>
+hipError_t launch_typed(const GrpoArgs& a) {
+  return a.V % TI::kVec == 0 ? launch_vec<TI, true>(a) : launch_vec<TI, false>(a);
 }
 
 }  // namespace

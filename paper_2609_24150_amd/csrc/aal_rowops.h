@@ -1,5 +1,4 @@
-// Workgroup-per-row building blocks shared by the streaming kernels: one
-// 256-thread workgroup reduces one logit row.
+// Workgroup-per-row building blocks shared by the streaming kernels.
 #pragma once
 
 #include "aal_device.h"
@@ -10,21 +9,144 @@ namespace aal {
 
 constexpr int kRowBlock = 256;
 constexpr int kRowWaves = kRowBlock / kWave;
+constexpr int kWideBlock = 1024;
 
+// Workgroup size of a pass that reduces one row per workgroup.  Up to 512
+// rows of more than 8192 entries take 1024 threads each: 256-thread workgroups
+// (eight per CU) would leave wavefront slots empty below 2048 rows (EAL over 45
+// rows of 129,076, with the split gradient pass below: 284 -> 38 us).  768 rows
+// of 50,001 are slower that way (KL + TV call 144 -> 162 us: 768 workgroups of
+// 1024 threads need two rounds of the device, the second half empty).
+static inline bool wide_rows(int64_t rows, int V) { return rows <= 512 && V > 8192; }
 
-// Element group `gi` of a row: one 16-byte vector (VEC) or one element.
-template <class TI, bool VEC>
-struct Groups {
-  static constexpr int E = VEC ? TI::kVec : 1;
-  static __device__ __forceinline__ void load(const void* base, int64_t g0, int64_t gi, float (&x)[E]) {
-    if constexpr (VEC) {
-      TI::unpack(ldvec_nt(base, g0 + gi), x);
+// Workgroups per row of a pass without a reduction (the gradient passes): as
+// many as bring the launch to 2048 workgroups of 256 threads, eight per CU,
+// each with at least one round of U vectors per thread.
+static inline unsigned row_splits(int64_t rows, int V, int vec, int U) {
+  const int64_t rounds = (int64_t(V) / vec + kRowBlock * U - 1) / (kRowBlock * U);
+  const int64_t want = (2048 + rows - 1) / rows;
+  return unsigned(want < rounds ? want : rounds > 0 ? rounds : 1);
+}
+
+// The 16-byte vectors that cover one row of V elements.  ALIGNED: V is a
+// multiple of the vector, so every row is whole vectors.  Otherwise a row
+// starts `head` elements past a vector boundary (all logit and gradient arrays
+// are 16-byte aligned and share the element index, so a row has the same
+// phase in each of them): its first and last vectors are shared with the
+// neighbouring rows and are loaded whole like the others, then the elements
+// outside the row become -inf.  Only the array's very last vector, which may
+// reach past the allocation, is read element by element, and the stores at a
+// row's edges go element by element.  Against element-by-element accesses of
+// the whole row: the simulation over 447,252 rows of 2,587 bf16 logits 4.12 ->
+// 1.51 ms, the KL + TV passes over 768 rows of 50,001 145 + 77 -> 83 + 47 us,
+// the WTV passes over 1792 rows of 32,001 117 + 75 -> 94 + 70 us.
+template <class TI, bool ALIGNED>
+struct RowVecs {
+  static constexpr int E = TI::kVec;
+  int64_t g0;  // vector index of the row's first vector
+  int ng;      // vectors that cover the row
+  int nfull;   // of them, those that lie inside the array
+  int head;    // elements of the first vector before the row
+  int V;
+
+  __device__ __forceinline__ RowVecs(int64_t row, int64_t rows, int v) : V(v) {
+    if constexpr (ALIGNED) {
+      nfull = ng = v / E;
+      g0 = row * int64_t(ng);
+      head = 0;
     } else {
-      x[0] = TI::load1(base, g0 + gi);
+      const int64_t e0 = row * int64_t(v);
+      g0 = e0 / E;
+      head = int(e0 - g0 * E);
+      ng = int((int64_t(head) + v + E - 1) / E);
+      nfull = int(min(int64_t(ng), rows * v / E - g0));
+    }
+  }
+  // index in the row of element e of vector gi (outside [0, V) at the edges)
+  __device__ __forceinline__ int index(int gi, int e) const { return gi * E + e - head; }
+  __device__ __forceinline__ bool whole(int gi) const {
+    return ALIGNED || (index(gi, 0) >= 0 && index(gi, 0) <= V - E);
+  }
+  __device__ __forceinline__ u32x4 raw(const void* base, int gi) const {
+    return __builtin_nontemporal_load(static_cast<const u32x4*>(base) + g0 + gi);
+  }
+  // the elements of an edge vector, with -inf outside the row
+  __device__ __forceinline__ u32x4 edge(const void* base, int gi, u32x4 w) const {
+    using T = typename TI::storage;
+    T x[E];
+    __builtin_memcpy(x, &w, sizeof w);
+#pragma unroll
+    for (int e = 0; e < E; ++e) {
+      const int i = index(gi, e);
+      if (i < 0 || i >= V)
+        x[e] = TI::neg_inf();
+      else if (gi >= nfull)
+        x[e] = static_cast<const T*>(base)[(g0 + gi) * E + e];
+    }
+    __builtin_memcpy(&w, x, sizeof w);
+    return w;
+  }
+  static __device__ __forceinline__ u32x4 none() {
+    typename TI::storage x[E];
+#pragma unroll
+    for (int e = 0; e < E; ++e) x[e] = TI::neg_inf();
+    u32x4 w;
+    __builtin_memcpy(&w, x, sizeof w);
+    return w;
+  }
+  // vector gi, -inf outside the row
+  __device__ __forceinline__ u32x4 load(const void* base, int gi) const {
+    u32x4 w = none();
+    if (gi < nfull) w = raw(base, gi);
+    if (!whole(gi) && gi < ng) w = edge(base, gi, w);
+    return w;
+  }
+  // U vectors of each of N arrays, `step` apart from vector `base` on: the
+  // loads are issued together, the edges are mended afterwards.
+  template <int N, int U>
+  __device__ __forceinline__ void load(const void* const (&p)[N], int base, int step, u32x4 (&w)[N][U]) const {
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+      const int gi = base + u * step;
+      if (gi < nfull) {
+#pragma unroll
+        for (int n = 0; n < N; ++n) w[n][u] = raw(p[n], gi);
+      } else {
+#pragma unroll
+        for (int n = 0; n < N; ++n) w[n][u] = none();
+      }
+    }
+    if constexpr (!ALIGNED) {
+#pragma unroll
+      for (int u = 0; u < U; ++u) {
+        const int gi = base + u * step;
+        if (!whole(gi) && gi < ng) {
+#pragma unroll
+          for (int n = 0; n < N; ++n) w[n][u] = edge(p[n], gi, w[n][u]);
+        }
+      }
+    }
+  }
+  template <int U>
+  static __device__ __forceinline__ void unpack(const u32x4 (&w)[U], float (&x)[U][E]) {
+#pragma unroll
+    for (int u = 0; u < U; ++u) TI::unpack(to_uint4(w[u]), x[u]);
+  }
+  template <class TG>
+  __device__ __forceinline__ void store(void* base, int gi, const float (&g)[E]) const {
+    if (whole(gi)) {
+      store_vec<TG, E>(base, (g0 + gi) * E, g);
+      return;
+    }
+#pragma unroll
+    for (int e = 0; e < E; ++e) {
+      const int i = index(gi, e);
+      if (i >= 0 && i < V) TG::store1(base, (g0 + gi) * E + e, g[e]);
     }
   }
 };
 
+template <int WAVES>
 static __device__ LseState block_lse(LseState st, float sc, LseState* sh) {
   st = wave_lse(st, sc);
   const int w = threadIdx.x / kWave;
@@ -32,11 +154,12 @@ static __device__ LseState block_lse(LseState st, float sc, LseState* sh) {
   __syncthreads();
   LseState r = sh[0];
 #pragma unroll
-  for (int i = 1; i < kRowWaves; ++i) r = lse_merge(r, sh[i], sc);
+  for (int i = 1; i < WAVES; ++i) r = lse_merge(r, sh[i], sc);
   __syncthreads();
   return r;
 }
 
+template <int WAVES>
 static __device__ float block_sum(float v, float* sh) {
   v = wave_sum(v);
   const int w = threadIdx.x / kWave;
@@ -44,12 +167,13 @@ static __device__ float block_sum(float v, float* sh) {
   __syncthreads();
   float r = sh[0];
 #pragma unroll
-  for (int i = 1; i < kRowWaves; ++i) r += sh[i];
+  for (int i = 1; i < WAVES; ++i) r += sh[i];
   __syncthreads();
   return r;
 }
 
 // Largest value, lowest index among equal values.
+template <int WAVES>
 static __device__ int block_argmax(float best, int idx, float* shf, int* shi) {
   const float wm = wave_max(best);
   const int wi = wave_min_i(best == wm ? idx : INT_MAX);
@@ -62,7 +186,7 @@ static __device__ int block_argmax(float best, int idx, float* shf, int* shi) {
   float m = shf[0];
   int i = shi[0];
 #pragma unroll
-  for (int k = 1; k < kRowWaves; ++k) {
+  for (int k = 1; k < WAVES; ++k) {
     if (shf[k] > m || (shf[k] == m && shi[k] < i)) {
       m = shf[k];
       i = shi[k];

@@ -15,68 +15,49 @@
 //                 rollouts (Eq. advantage), optionally clipped.
 #include "aal_device.h"
 #include "aal_internal.h"
+#include "aal_rowops.h"
 
 namespace aal {
 namespace {
 
-constexpr int kBlock = 256;
-constexpr int kWaves = kBlock / kWave;
+constexpr int kBlock = kRowBlock;
+constexpr int kWaves = kRowWaves;
 
 static __device__ __forceinline__ double bcast_d(double v, int lane) { return __shfl(v, lane, 64); }
-
-template <class TI, bool VEC>
-struct SimGroups {
-  static constexpr int E = VEC ? TI::kVec : 1;
-  static __device__ __forceinline__ void load(const void* base, int64_t g0, int gi, int ng, float (&x)[E]) {
-    if (gi < ng) {
-      if constexpr (VEC) {
-        TI::unpack(ldvec_nt(base, g0 + gi), x);
-      } else {
-        x[0] = TI::load1(base, g0 + gi);
-      }
-    } else {
-#pragma unroll
-      for (int e = 0; e < E; ++e) x[e] = kNegInf;
-    }
-  }
-};
 
 // Mass of tile t relative to the row reference msc: sum_t * 2^(msc_t - msc).
 static __device__ __forceinline__ double tile_mass(const float2* ts, int t, float msc) {
   return double(ts[t].y) * double(ex2(ts[t].x - msc));
 }
 
-template <class TI, bool VEC, int U>
-__global__ __launch_bounds__(kBlock) void k_sim_rows(const void* __restrict__ zd, const void* __restrict__ zt, int V,
+template <class TI, bool VEC, int U, int BLK>
+__global__ __launch_bounds__(BLK) void k_sim_rows(const void* __restrict__ zd, const void* __restrict__ zt, int V,
                                                      float sc, const float* __restrict__ u1,
                                                      const float* __restrict__ u2, int32_t* __restrict__ token,
                                                      int32_t* __restrict__ accept) {
-  using Gr = SimGroups<TI, VEC>;
-  constexpr int E = Gr::E;
+  using Rv = RowVecs<TI, VEC>;
+  constexpr int E = Rv::E;
   constexpr int TG = kWave * U;  // element groups per tile
   extern __shared__ float2 tile_stat[];  // (msc_t, sum_t) per tile
-  __shared__ LseState sh_lse[kWaves];
+  __shared__ LseState sh_lse[BLK / kWave];
   __shared__ int sh_ctile;
   __shared__ double sh_base, sh_theta;
   __shared__ float sh_msc, sh_l2s;
 
   const int64_t row = blockIdx.x;
-  const int ng = V / E;
-  const int ntiles = (ng + TG - 1) / TG;
-  const int64_t g0 = row * int64_t(ng);
+  const Rv rv(row, gridDim.x, V);
+  const int ntiles = (rv.ng + TG - 1) / TG;
   const int64_t e0 = row * int64_t(V);
   const int w = threadIdx.x / kWave;
   const int lane = threadIdx.x & (kWave - 1);
 
   LseState st = lse_init();
-  for (int t = w; t < ntiles; t += kWaves) {
+  for (int t = w; t < ntiles; t += BLK / kWave) {
+    u32x4 w[2][U];
     float xd[U][E], xt[U][E];
-#pragma unroll
-    for (int u = 0; u < U; ++u) {
-      const int gi = t * TG + u * kWave + lane;
-      Gr::load(zd, g0, gi, ng, xd[u]);
-      Gr::load(zt, g0, gi, ng, xt[u]);
-    }
+    rv.load({zd, zt}, t * TG + lane, kWave, w);
+    rv.unpack(w[0], xd);
+    rv.unpack(w[1], xt);
     float lm = kNegInf;
 #pragma unroll
     for (int u = 0; u < U; ++u)
@@ -117,7 +98,7 @@ __global__ __launch_bounds__(kBlock) void k_sim_rows(const void* __restrict__ zd
     __syncthreads();
     st = sh_lse[0];
 #pragma unroll
-    for (int i = 1; i < kWaves; ++i) st = lse_merge(st, sh_lse[i], sc);
+    for (int i = 1; i < BLK / kWave; ++i) st = lse_merge(st, sh_lse[i], sc);
   }
 
   // Wave 0: locate the tile whose cumulative draft mass crosses u1 * total.
@@ -177,7 +158,7 @@ __global__ __launch_bounds__(kBlock) void k_sim_rows(const void* __restrict__ zd
     for (int u = 0; u < U; ++u) {
       const int gi = ct * TG + u * kWave + lane;
       float xd[E], ev[E];
-      Gr::load(zd, g0, gi, ng, xd);
+      TI::unpack(to_uint4(rv.load(zd, gi)), xd);
       double ls = 0.0;
 #pragma unroll
       for (int e = 0; e < E; ++e) {
@@ -202,7 +183,7 @@ __global__ __launch_bounds__(kBlock) void k_sim_rows(const void* __restrict__ zd
             if (xi < 0 && c > theta) xi = e;
           }
           if (xi < 0) xi = last_pos >= 0 ? last_pos : 0;
-          xi += gi * E;
+          xi = min(max(rv.index(gi, xi), 0), V - 1);
         }
         x = __shfl(xi, L, 64);
       }
@@ -216,11 +197,11 @@ __global__ __launch_bounds__(kBlock) void k_sim_rows(const void* __restrict__ zd
       for (int u = 0; u < U; ++u) {
         const int gi = ct * TG + u * kWave + lane;
         float xd[E];
-        Gr::load(zd, g0, gi, ng, xd);
+        TI::unpack(to_uint4(rv.load(zd, gi)), xd);
 #pragma unroll
         for (int e = 0; e < E; ++e) {
-          if (xd[e] != kNegInf) fin = max(fin, gi * E + e);
-          if (ex2(__builtin_fmaf(xd[e], sc, -msc)) > 0.f) pos = max(pos, gi * E + e);
+          if (xd[e] != kNegInf) fin = max(fin, rv.index(gi, e));
+          if (ex2(__builtin_fmaf(xd[e], sc, -msc)) > 0.f) pos = max(pos, rv.index(gi, e));
         }
       }
       for (int off = 32; off > 0; off >>= 1) {
@@ -278,28 +259,35 @@ __global__ __launch_bounds__(kBlock) void k_group_adv(const int32_t* __restrict_
   }
 }
 
-template <class TI, bool VEC, int U>
+template <class TI, bool VEC, int U, int BLK>
 hipError_t launch_rows(const SimArgs& a) {
-  constexpr int E = VEC ? TI::kVec : 1;
-  const int ng = a.V / E;
+  constexpr int E = TI::kVec;
+  // a row that starts and ends inside vectors touches up to one more of them
+  const int ng = VEC ? a.V / E : (a.V + 2 * (E - 1)) / E;
   const int ntiles = (ng + kWave * U - 1) / (kWave * U);
   const size_t lds = size_t(ntiles) * sizeof(float2);
   const int64_t rows = int64_t(a.P) * a.G * a.K;
-  k_sim_rows<TI, VEC, U><<<dim3(unsigned(rows)), kBlock, lds, a.stream>>>(a.zd, a.zt, a.V, a.sc, a.u1, a.u2,
+  k_sim_rows<TI, VEC, U, BLK><<<dim3(unsigned(rows)), BLK, lds, a.stream>>>(a.zd, a.zt, a.V, a.sc, a.u1, a.u2,
                                                                           a.token, a.accept);
   return hipGetLastError();
 }
 
+template <class TI, bool VEC>
+hipError_t launch_rows_v(const SimArgs& a) {
+  return wide_rows(int64_t(a.P) * a.G * a.K, a.V) ? launch_rows<TI, VEC, 2, kWideBlock>(a)
+                                                  : launch_rows<TI, VEC, 2, kBlock>(a);
+}
+
 template <class TI>
 hipError_t launch_rows_t(const SimArgs& a) {
-  if (a.V % TI::kVec == 0) return launch_rows<TI, true, 2>(a);
-  return launch_rows<TI, false, 8>(a);
+  return a.V % TI::kVec == 0 ? launch_rows_v<TI, true>(a) : launch_rows_v<TI, false>(a);
 }
 
 }  // namespace
 
-// Largest tile count: V <= 2^21 with 512-element tiles.
-static_assert(sizeof(float2) * ((1 << 21) / 512) <= 32768, "tile table fits in 32 KiB of LDS");
+// Largest tile count: V <= 2^21 with 512-element tiles, one more for a row
+// that starts inside a vector.
+static_assert(sizeof(float2) * ((1 << 21) / 512 + 1) <= 33 * 1024, "the tile table fits in LDS");
 
 hipError_t launch_sim(const SimArgs& a) {
   hipError_t e = (a.in == DType::kBf16) ? launch_rows_t<Bf16>(a) : launch_rows_t<F32>(a);

@@ -25,38 +25,30 @@ namespace {
 constexpr int kBlock = kRowBlock;
 constexpr int kWaves = kRowWaves;
 
-template <class TI, int MODE, bool VEC, int U>
-__global__ __launch_bounds__(kBlock) void k_row_stats(const void* __restrict__ zd, const void* __restrict__ zt,
+template <class TI, int MODE, bool VEC, int U, int BLK>
+__global__ __launch_bounds__(BLK) void k_row_stats(const void* __restrict__ zd, const void* __restrict__ zt,
                                                       int V, float scd, float sct,
                                                       RowStats* __restrict__ stats) {
-  using Gr = Groups<TI, VEC>;
-  constexpr int E = Gr::E;
-  __shared__ LseState sh_lse[kWaves];
-  __shared__ float sh_f[kWaves];
-  __shared__ int sh_i[kWaves];
+  using Rv = RowVecs<TI, VEC>;
+  constexpr int E = Rv::E;
+  __shared__ LseState sh_lse[BLK / kWave];
+  __shared__ float sh_f[BLK / kWave];
+  __shared__ int sh_i[BLK / kWave];
 
   const int64_t row = blockIdx.x;
-  const int ng = V / E;
-  const int64_t g0 = row * int64_t(ng);
+  const Rv rv(row, gridDim.x, V);
   const int64_t e0 = row * int64_t(V);
 
   LseState sd = lse_init(), st = lse_init();
   float best = kNegInf;
   int bidx = INT_MAX;
 
-  for (int base = threadIdx.x; base < ng; base += kBlock * U) {
+  for (int base = threadIdx.x; base < rv.ng; base += BLK * U) {
+    u32x4 w[2][U];
     float xd[U][E], xt[U][E];
-#pragma unroll
-    for (int u = 0; u < U; ++u) {
-      const int gi = base + u * kBlock;
-      if (gi < ng) {
-        Gr::load(zd, g0, gi, xd[u]);
-        Gr::load(zt, g0, gi, xt[u]);
-      } else {
-#pragma unroll
-        for (int e = 0; e < E; ++e) xd[u][e] = xt[u][e] = kNegInf;
-      }
-    }
+    rv.load({zd, zt}, base, BLK, w);
+    rv.unpack(w[0], xd);
+    rv.unpack(w[1], xt);
     float cm = kNegInf;
 #pragma unroll
     for (int u = 0; u < U; ++u)
@@ -91,19 +83,19 @@ __global__ __launch_bounds__(kBlock) void k_row_stats(const void* __restrict__ z
         for (int e = 0; e < E; ++e)
           if (xt[u][e] > best) {
             best = xt[u][e];
-            bidx = (base + u * kBlock) * E + e;
+            bidx = rv.index(base + u * BLK, e);
           }
     }
   }
 
-  sd = block_lse(sd, scd, sh_lse);
+  sd = block_lse<BLK / kWave>(sd, scd, sh_lse);
   const float l2sd = __log2f(sd.s);
   RowStats out;
   out.msc_d = sd.msc;
   out.l2s_d = l2sd;
   out.coef = 0.f;
   if constexpr (MODE == int(Mode::kEal)) {
-    int x = block_argmax(best, bidx, sh_f, sh_i);
+    int x = block_argmax<BLK / kWave>(best, bidx, sh_f, sh_i);
     if (x == INT_MAX) x = 0;  // a row with no finite target logit: unspecified, stay in bounds
     const float zx = TI::load1(zd, e0 + x);
     out.a = ex2(__builtin_fmaf(zx, scd, -sd.msc) - l2sd);
@@ -112,22 +104,15 @@ __global__ __launch_bounds__(kBlock) void k_row_stats(const void* __restrict__ z
     out.l2s_t = 0.f;
     out.qlt = 0.f;
   } else {
-    st = block_lse(st, sct, sh_lse);
+    st = block_lse<BLK / kWave>(st, sct, sh_lse);
     const float l2st = __log2f(st.s);
     float smin = 0.f, qlt = 0.f;
-    for (int base = threadIdx.x; base < ng; base += kBlock * U) {
+    for (int base = threadIdx.x; base < rv.ng; base += BLK * U) {
+      u32x4 w[2][U];
       float xd[U][E], xt[U][E];
-#pragma unroll
-      for (int u = 0; u < U; ++u) {
-        const int gi = base + u * kBlock;
-        if (gi < ng) {
-          Gr::load(zd, g0, gi, xd[u]);
-          Gr::load(zt, g0, gi, xt[u]);
-        } else {
-#pragma unroll
-          for (int e = 0; e < E; ++e) xd[u][e] = xt[u][e] = kNegInf;
-        }
-      }
+      rv.load({zd, zt}, base, BLK, w);
+      rv.unpack(w[0], xd);
+      rv.unpack(w[1], xt);
       float am = 0.f, aq = 0.f;
 #pragma unroll
       for (int u = 0; u < U; ++u)
@@ -142,8 +127,8 @@ __global__ __launch_bounds__(kBlock) void k_row_stats(const void* __restrict__ z
       smin += am;
       qlt += aq;
     }
-    smin = block_sum(smin, sh_f);
-    qlt = block_sum(qlt, sh_f);
+    smin = block_sum<BLK / kWave>(smin, sh_f);
+    qlt = block_sum<BLK / kWave>(qlt, sh_f);
     out.a = smin;
     out.qlt = qlt;
     out.msc_t = st.msc;
@@ -205,32 +190,37 @@ template <class TI, class TG, int MODE, bool VEC, int U>
 __global__ __launch_bounds__(kBlock) void k_grad(const void* __restrict__ zd, const void* __restrict__ zt, int V,
                                                  float scd, float sct, const RowStats* __restrict__ stats,
                                                  void* __restrict__ grad) {
-  using Gr = Groups<TI, VEC>;
-  constexpr int E = Gr::E;
+  using Rv = RowVecs<TI, VEC>;
+  constexpr int E = Rv::E;
+  constexpr int NT = MODE == int(Mode::kEal) ? 1 : 2;  // logit arrays read
   const int64_t row = blockIdx.x;
-  const int ng = V / E;
-  const int64_t g0 = row * int64_t(ng);
+  const Rv rv(row, gridDim.x, V);
   const RowStats s = stats[row];
   const float c = s.coef;
   const float cA = c * (1.f - s.qlt);  // WTV, entries with q < p
   const float cB = -c * s.qlt;         // WTV, the others
-  for (int base = threadIdx.x; base < ng; base += kBlock * U) {
+  for (int base = blockIdx.y * kBlock * U + threadIdx.x; base < rv.ng; base += gridDim.y * kBlock * U) {
+    u32x4 w[NT][U];  // loaded together: a launch of few wavefronts waits once per round
+    if constexpr (NT == 2)
+      rv.load({zd, zt}, base, kBlock, w);
+    else
+      rv.load({zd}, base, kBlock, w);
 #pragma unroll
     for (int u = 0; u < U; ++u) {
       const int gi = base + u * kBlock;
-      if (gi >= ng) break;
+      if (gi >= rv.ng) break;
       float xd[E], g[E];
-      Gr::load(zd, g0, gi, xd);
+      TI::unpack(to_uint4(w[0][u]), xd);
       if constexpr (MODE == int(Mode::kEal)) {
 #pragma unroll
         for (int e = 0; e < E; ++e) {
           const float q = ex2(__builtin_fmaf(xd[e], scd, -s.msc_d) - s.l2s_d);
-          const float d = (gi * E + e == s.xstar) ? 1.f : 0.f;
+          const float d = (rv.index(gi, e) == s.xstar) ? 1.f : 0.f;
           g[e] = c * (d - q);
         }
       } else {
         float xt[E];
-        Gr::load(zt, g0, gi, xt);
+        TI::unpack(to_uint4(w[NT - 1][u]), xt);
 #pragma unroll
         for (int e = 0; e < E; ++e) {
           const float ld = __builtin_fmaf(xd[e], scd, -s.msc_d) - s.l2s_d;
@@ -239,49 +229,47 @@ __global__ __launch_bounds__(kBlock) void k_grad(const void* __restrict__ zd, co
           g[e] = q * ((ld < lt) ? cA : cB);
         }
       }
-      if constexpr (VEC) {
-        store_vec<TG, E>(grad, (g0 + gi) * E, g);
-      } else {
-        TG::store1(grad, g0 + gi, g[0]);
-      }
+      rv.template store<TG>(grad, gi, g);
     }
   }
 }
 
-template <class TI, int MODE>
-hipError_t launch_typed(const LossArgs& a) {
+template <class TI, int MODE, bool VEC, int BLK>
+void stats_launch(const LossArgs& a) {
+  k_row_stats<TI, MODE, VEC, 4, BLK><<<dim3(unsigned(a.N * a.K)), BLK, 0, a.stream>>>(a.zd, a.zt, a.V, a.sc_d, a.sc_t,
+                                                                                     a.ws.stats);
+}
+
+template <class TI, class TG, int MODE, bool VEC>
+void grad_launch(const LossArgs& a) {
+  constexpr int U = 4;
   const int64_t rows = a.N * a.K;
-  const bool vec = (a.V % TI::kVec) == 0;
-  constexpr int M = MODE;
-  if (vec) {
-    k_row_stats<TI, M, true, 4><<<dim3(unsigned(rows)), kBlock, 0, a.stream>>>(a.zd, a.zt, a.V, a.sc_d, a.sc_t,
-                                                                                a.ws.stats);
-  } else {
-    k_row_stats<TI, M, false, 8><<<dim3(unsigned(rows)), kBlock, 0, a.stream>>>(a.zd, a.zt, a.V, a.sc_d, a.sc_t,
-                                                                                 a.ws.stats);
-  }
+  k_grad<TI, TG, MODE, VEC, U><<<dim3(unsigned(rows), row_splits(rows, a.V, TI::kVec, U)), kBlock, 0, a.stream>>>(
+      a.zd, a.zt, a.V, a.sc_d, a.sc_t, a.ws.stats, a.grad);
+}
+
+template <class TI, int MODE, bool VEC>
+hipError_t launch_vec(const LossArgs& a) {
+  if (wide_rows(a.N * a.K, a.V))
+    stats_launch<TI, MODE, VEC, kWideBlock>(a);
+  else
+    stats_launch<TI, MODE, VEC, kBlock>(a);
   const unsigned wblocks = unsigned((a.N + kBlock - 1) / kBlock);
-  k_window_scan<<<wblocks, kBlock, 0, a.stream>>>(a.ws.stats, a.N, a.K, M, a.inv_t_d, a.grad_scale, a.window_e,
+  k_window_scan<<<wblocks, kBlock, 0, a.stream>>>(a.ws.stats, a.N, a.K, MODE, a.inv_t_d, a.grad_scale, a.window_e,
                                                   a.accept, a.xstar);
   k_loss<<<1, kBlock, 0, a.stream>>>(a.window_e, a.N, a.loss, nullptr);
   if (a.grad) {
-    if (a.gd == DType::kBf16) {
-      if (vec)
-        k_grad<TI, GBf16, M, true, 4><<<dim3(unsigned(rows)), kBlock, 0, a.stream>>>(a.zd, a.zt, a.V, a.sc_d,
-                                                                                     a.sc_t, a.ws.stats, a.grad);
-      else
-        k_grad<TI, GBf16, M, false, 8><<<dim3(unsigned(rows)), kBlock, 0, a.stream>>>(a.zd, a.zt, a.V, a.sc_d,
-                                                                                      a.sc_t, a.ws.stats, a.grad);
-    } else {
-      if (vec)
-        k_grad<TI, GF32, M, true, 4><<<dim3(unsigned(rows)), kBlock, 0, a.stream>>>(a.zd, a.zt, a.V, a.sc_d,
-                                                                                    a.sc_t, a.ws.stats, a.grad);
-      else
-        k_grad<TI, GF32, M, false, 8><<<dim3(unsigned(rows)), kBlock, 0, a.stream>>>(a.zd, a.zt, a.V, a.sc_d,
-                                                                                     a.sc_t, a.ws.stats, a.grad);
-    }
+    if (a.gd == DType::kBf16)
+      grad_launch<TI, GBf16, MODE, VEC>(a);
+    else
+      grad_launch<TI, GF32, MODE, VEC>(a);
   }
   return hipGetLastError();
+}
+
+template <class TI, int MODE>
+hipError_t launch_typed(const LossArgs& a) {
+  return a.V % TI::kVec == 0 ? launch_vec<TI, MODE, true>(a) : launch_vec<TI, MODE, false>(a);
 }
 
 }  // namespace

@@ -39,35 +39,33 @@ unsigned row_grid(int64_t rows) { return unsigned(rows < kMaxRowBlocks ? rows : 
 
 // LAB (EAL with labels): the label replaces the greedy token and the target
 // slice is not read.
-template <class TI, int MODE, bool VEC, int U, bool LAB>
-__global__ __launch_bounds__(kBlock) void k_vp_partials(const void* __restrict__ zd, const void* __restrict__ zt,
+template <class TI, int MODE, bool VEC, int U, bool LAB, int BLK>
+__global__ __launch_bounds__(BLK) void k_vp_partials(const void* __restrict__ zd, const void* __restrict__ zt,
                                                         const int32_t* __restrict__ labels, int64_t rows, int Vs,
                                                         int v0, int vtot, float scd, float sct,
                                                         aal_vp_part_t* __restrict__ parts) {
-  using Gr = Groups<TI, VEC>;
-  constexpr int E = Gr::E;
-  __shared__ LseState sh_lse[kWaves];
-  __shared__ float sh_f[kWaves];
-  __shared__ int sh_i[kWaves];
-  const int ng = Vs / E;
+  using Rv = RowVecs<TI, VEC>;
+  constexpr int E = Rv::E;
+  __shared__ LseState sh_lse[BLK / kWave];
+  __shared__ float sh_f[BLK / kWave];
+  __shared__ int sh_i[BLK / kWave];
 
   for (int64_t row = blockIdx.x; row < rows; row += gridDim.x) {
-    const int64_t g0 = row * int64_t(ng);
+    const Rv rv(row, rows, Vs);
     LseState sd = lse_init(), st = lse_init();
     float best = kNegInf;
     int bidx = INT_MAX;
-    for (int base = threadIdx.x; base < ng; base += kBlock * U) {
+    for (int base = threadIdx.x; base < rv.ng; base += BLK * U) {
       float xd[U][E], xt[U][E];
-#pragma unroll
-      for (int u = 0; u < U; ++u) {
-        const int gi = base + u * kBlock;
-        if (gi < ng) {
-          Gr::load(zd, g0, gi, xd[u]);
-          if constexpr (!LAB) Gr::load(zt, g0, gi, xt[u]);
-        } else {
-#pragma unroll
-          for (int e = 0; e < E; ++e) xd[u][e] = xt[u][e] = kNegInf;
-        }
+      if constexpr (!LAB) {
+        u32x4 w[2][U];
+        rv.load({zd, zt}, base, BLK, w);
+        rv.unpack(w[0], xd);
+        rv.unpack(w[1], xt);
+      } else {
+        u32x4 w[1][U];
+        rv.load({zd}, base, BLK, w);
+        rv.unpack(w[0], xd);
       }
       float cm = kNegInf;
 #pragma unroll
@@ -103,11 +101,11 @@ __global__ __launch_bounds__(kBlock) void k_vp_partials(const void* __restrict__
           for (int e = 0; e < E; ++e)
             if (xt[u][e] > best) {
               best = xt[u][e];
-              bidx = (base + u * kBlock) * E + e;
+              bidx = rv.index(base + u * BLK, e);
             }
       }
     }
-    sd = block_lse(sd, scd, sh_lse);
+    sd = block_lse<BLK / kWave>(sd, scd, sh_lse);
     aal_vp_part_t out;
     out.zmax_d = sd.m;
     out.s_d = sd.s;
@@ -128,7 +126,7 @@ __global__ __launch_bounds__(kBlock) void k_vp_partials(const void* __restrict__
       }
       out.s_t = 0.f;
     } else if constexpr (MODE == int(Mode::kEal)) {
-      const int x = block_argmax(best, bidx, sh_f, sh_i);
+      const int x = block_argmax<BLK / kWave>(best, bidx, sh_f, sh_i);
       const int64_t e0 = row * int64_t(Vs);
       if (x == INT_MAX) {
         out.zmax_t = kNegInf;
@@ -141,7 +139,7 @@ __global__ __launch_bounds__(kBlock) void k_vp_partials(const void* __restrict__
       }
       out.s_t = 0.f;
     } else {
-      st = block_lse(st, sct, sh_lse);
+      st = block_lse<BLK / kWave>(st, sct, sh_lse);
       out.zmax_t = st.m;
       out.s_t = st.s;
       out.zd_at = 0.f;
@@ -209,32 +207,24 @@ __global__ __launch_bounds__(kBlock) void k_vp_merge(const aal_vp_part_t* __rest
   out[row] = o;
 }
 
-template <class TI, bool VEC, int U>
-__global__ __launch_bounds__(kBlock) void k_vp_accept(const void* __restrict__ zd, const void* __restrict__ zt,
+template <class TI, bool VEC, int U, int BLK>
+__global__ __launch_bounds__(BLK) void k_vp_accept(const void* __restrict__ zd, const void* __restrict__ zt,
                                                       int64_t rows, int Vs, float scd, float sct,
                                                       const aal_vp_row_t* __restrict__ rec,
                                                       aal_vp_acc_t* __restrict__ acc) {
-  using Gr = Groups<TI, VEC>;
-  constexpr int E = Gr::E;
-  __shared__ float sh_f[kWaves];
-  const int ng = Vs / E;
+  using Rv = RowVecs<TI, VEC>;
+  constexpr int E = Rv::E;
+  __shared__ float sh_f[BLK / kWave];
   for (int64_t row = blockIdx.x; row < rows; row += gridDim.x) {
-    const int64_t g0 = row * int64_t(ng);
+    const Rv rv(row, rows, Vs);
     const aal_vp_row_t s = rec[row];
     float smin = 0.f, qlt = 0.f;
-    for (int base = threadIdx.x; base < ng; base += kBlock * U) {
+    for (int base = threadIdx.x; base < rv.ng; base += BLK * U) {
+      u32x4 w[2][U];
       float xd[U][E], xt[U][E];
-#pragma unroll
-      for (int u = 0; u < U; ++u) {
-        const int gi = base + u * kBlock;
-        if (gi < ng) {
-          Gr::load(zd, g0, gi, xd[u]);
-          Gr::load(zt, g0, gi, xt[u]);
-        } else {
-#pragma unroll
-          for (int e = 0; e < E; ++e) xd[u][e] = xt[u][e] = kNegInf;
-        }
-      }
+      rv.load({zd, zt}, base, BLK, w);
+      rv.unpack(w[0], xd);
+      rv.unpack(w[1], xt);
       float am = 0.f, aq = 0.f;
 #pragma unroll
       for (int u = 0; u < U; ++u)
@@ -249,8 +239,8 @@ __global__ __launch_bounds__(kBlock) void k_vp_accept(const void* __restrict__ z
       smin += am;
       qlt += aq;
     }
-    smin = block_sum(smin, sh_f);
-    qlt = block_sum(qlt, sh_f);
+    smin = block_sum<BLK / kWave>(smin, sh_f);
+    qlt = block_sum<BLK / kWave>(qlt, sh_f);
     if (threadIdx.x == 0) acc[row] = aal_vp_acc_t{smin, qlt};
   }
 }
@@ -365,33 +355,38 @@ template <class TI, class TG, int MODE, bool VEC, int U>
 __global__ __launch_bounds__(kBlock) void k_vp_grad(const void* __restrict__ zd, const void* __restrict__ zt,
                                                     int64_t rows, int Vs, int v0, float scd, float sct,
                                                     const aal_vp_row_t* __restrict__ rec, void* __restrict__ grad) {
-  using Gr = Groups<TI, VEC>;
-  constexpr int E = Gr::E;
-  const int ng = Vs / E;
+  using Rv = RowVecs<TI, VEC>;
+  constexpr int E = Rv::E;
+  constexpr int NT = MODE == int(Mode::kEal) ? 1 : 2;  // logit arrays read
   for (int64_t row = blockIdx.x; row < rows; row += gridDim.x) {
-    const int64_t g0 = row * int64_t(ng);
+    const Rv rv(row, rows, Vs);
     const aal_vp_row_t s = rec[row];
     const float c = s.coef;
     const float cA = c * (1.f - s.qlt);  // WTV, entries with q < p
     const float cB = -c * s.qlt;         // WTV, the others
     const int64_t xl = int64_t(s.xstar) - v0;  // EAL: x* in slice coordinates (may lie outside)
-    for (int base = threadIdx.x; base < ng; base += kBlock * U) {
+    for (int base = blockIdx.y * kBlock * U + threadIdx.x; base < rv.ng; base += gridDim.y * kBlock * U) {
+      u32x4 w[NT][U];
+      if constexpr (NT == 2)
+        rv.load({zd, zt}, base, kBlock, w);
+      else
+        rv.load({zd}, base, kBlock, w);
 #pragma unroll
       for (int u = 0; u < U; ++u) {
         const int gi = base + u * kBlock;
-        if (gi >= ng) break;
+        if (gi >= rv.ng) break;
         float xd[E], g[E];
-        Gr::load(zd, g0, gi, xd);
+        TI::unpack(to_uint4(w[0][u]), xd);
         if constexpr (MODE == int(Mode::kEal)) {
 #pragma unroll
           for (int e = 0; e < E; ++e) {
             const float q = ex2(__builtin_fmaf(xd[e], scd, -s.msc_d) - s.l2s_d);
-            const float d = (int64_t(gi) * E + e == xl) ? 1.f : 0.f;
+            const float d = (rv.index(gi, e) == xl) ? 1.f : 0.f;
             g[e] = c * (d - q);
           }
         } else {
           float xt[E];
-          Gr::load(zt, g0, gi, xt);
+          TI::unpack(to_uint4(w[NT - 1][u]), xt);
 #pragma unroll
           for (int e = 0; e < E; ++e) {
             const float ld = __builtin_fmaf(xd[e], scd, -s.msc_d) - s.l2s_d;
@@ -400,25 +395,26 @@ __global__ __launch_bounds__(kBlock) void k_vp_grad(const void* __restrict__ zd,
             g[e] = q * ((ld < lt) ? cA : cB);
           }
         }
-        if constexpr (VEC) {
-          store_vec<TG, E>(grad, (g0 + gi) * E, g);
-        } else {
-          TG::store1(grad, g0 + gi, g[0]);
-        }
+        rv.template store<TG>(grad, gi, g);
       }
     }
   }
 }
 
+template <class TI, int MODE, bool LAB, bool VEC, int BLK>
+void partials_blk(const VpSlice& s, aal_vp_part_t* parts) {
+  k_vp_partials<TI, MODE, VEC, 4, LAB, BLK><<<row_grid(s.rows), BLK, 0, s.stream>>>(
+      s.zd, s.zt, s.labels, s.rows, s.vs, s.v0, s.vtot, s.scd, s.sct, parts);
+}
+
 template <class TI, int MODE, bool LAB>
 void partials_lab(const VpSlice& s, aal_vp_part_t* parts) {
-  const unsigned grid = row_grid(s.rows);
-  if (s.vs % TI::kVec == 0)
-    k_vp_partials<TI, MODE, true, 4, LAB><<<grid, kBlock, 0, s.stream>>>(s.zd, s.zt, s.labels, s.rows, s.vs, s.v0, s.vtot,
-                                                                          s.scd, s.sct, parts);
+  const bool vec = s.vs % TI::kVec == 0;
+  if (wide_rows(s.rows, s.vs))
+    vec ? partials_blk<TI, MODE, LAB, true, kWideBlock>(s, parts)
+        : partials_blk<TI, MODE, LAB, false, kWideBlock>(s, parts);
   else
-    k_vp_partials<TI, MODE, false, 8, LAB><<<grid, kBlock, 0, s.stream>>>(s.zd, s.zt, s.labels, s.rows, s.vs, s.v0, s.vtot,
-                                                                           s.scd, s.sct, parts);
+    vec ? partials_blk<TI, MODE, LAB, true, kBlock>(s, parts) : partials_blk<TI, MODE, LAB, false, kBlock>(s, parts);
 }
 
 template <class TI, int MODE>
@@ -432,24 +428,31 @@ void partials_typed(const VpSlice& s, aal_vp_part_t* parts) {
   partials_lab<TI, MODE, false>(s, parts);
 }
 
+template <class TI, bool VEC, int BLK>
+void accept_blk(const VpSlice& s, const aal_vp_row_t* row, aal_vp_acc_t* acc) {
+  k_vp_accept<TI, VEC, 4, BLK>
+      <<<row_grid(s.rows), BLK, 0, s.stream>>>(s.zd, s.zt, s.rows, s.vs, s.scd, s.sct, row, acc);
+}
+
 template <class TI>
 void accept_typed(const VpSlice& s, const aal_vp_row_t* row, aal_vp_acc_t* acc) {
-  const unsigned grid = row_grid(s.rows);
-  if (s.vs % TI::kVec == 0)
-    k_vp_accept<TI, true, 4><<<grid, kBlock, 0, s.stream>>>(s.zd, s.zt, s.rows, s.vs, s.scd, s.sct, row, acc);
+  const bool vec = s.vs % TI::kVec == 0;
+  if (wide_rows(s.rows, s.vs))
+    vec ? accept_blk<TI, true, kWideBlock>(s, row, acc) : accept_blk<TI, false, kWideBlock>(s, row, acc);
   else
-    k_vp_accept<TI, false, 8><<<grid, kBlock, 0, s.stream>>>(s.zd, s.zt, s.rows, s.vs, s.scd, s.sct, row, acc);
+    vec ? accept_blk<TI, true, kBlock>(s, row, acc) : accept_blk<TI, false, kBlock>(s, row, acc);
 }
 
 template <class TI, class TG, int MODE>
 void grad_typed(const VpSlice& s, const aal_vp_row_t* row, void* grad) {
-  const unsigned grid = row_grid(s.rows);
+  constexpr int U = 4;
+  const dim3 grid(row_grid(s.rows), row_splits(s.rows, s.vs, TI::kVec, U));
   if (s.vs % TI::kVec == 0)
-    k_vp_grad<TI, TG, MODE, true, 4><<<grid, kBlock, 0, s.stream>>>(s.zd, s.zt, s.rows, s.vs, s.v0, s.scd, s.sct,
-                                                                    row, grad);
+    k_vp_grad<TI, TG, MODE, true, U>
+        <<<grid, kBlock, 0, s.stream>>>(s.zd, s.zt, s.rows, s.vs, s.v0, s.scd, s.sct, row, grad);
   else
-    k_vp_grad<TI, TG, MODE, false, 8><<<grid, kBlock, 0, s.stream>>>(s.zd, s.zt, s.rows, s.vs, s.v0, s.scd, s.sct,
-                                                                     row, grad);
+    k_vp_grad<TI, TG, MODE, false, U>
+        <<<grid, kBlock, 0, s.stream>>>(s.zd, s.zt, s.rows, s.vs, s.v0, s.scd, s.sct, row, grad);
 }
 
 template <class TG>
