@@ -1,9 +1,10 @@
 // Register-resident schedule of the combined objectives: the instances for
-// fp32 logits (the kernel is in aal_resident_gen.h).
+// fp32 logits with an fp32 gradient and K up to 8 (the kernel is in aal_resident_gen.h;
+// the instances are spread over files so that they build in parallel).
 #include "aal_resident_gen.h"
 
 namespace aal {
 
-hipError_t launch_general_resident_f32(const GenArgs& a, bool* used) { return launch_ti<F32>(a, used); }
+hipError_t launch_general_resident_f32(const GenArgs& a, bool* used) { return launch_tg<F32, GF32, 1>(a, used); }
 
 }  // namespace aal

@@ -1,0 +1,10 @@
+// Register-resident schedule of the combined objectives: the instances for
+// fp32 logits with an fp32 gradient and K of 9 to 16 (the kernel is in aal_resident_gen.h;
+// the instances are spread over files so that they build in parallel).
+#include "aal_resident_gen.h"
+
+namespace aal {
+
+hipError_t launch_general_resident_f32_long(const GenArgs& a, bool* used) { return launch_tg<F32, GF32, 9>(a, used); }
+
+}  // namespace aal
