@@ -14,6 +14,7 @@ constexpr float kNegInf = -__builtin_huge_valf();
 // 8 bf16 or 4 fp32 elements.  bf16 -> fp32 is exact (a shift or a mask).
 struct Bf16 {
   using storage = uint16_t;
+  using bits = uint16_t;
   static constexpr int kVec = 8;
   static __device__ __forceinline__ storage neg_inf() { return 0xff80u; }
   static __device__ __forceinline__ void unpack(const uint4& w, float (&x)[8]) {
@@ -34,6 +35,7 @@ struct Bf16 {
 
 struct F32 {
   using storage = float;
+  using bits = uint32_t;
   static constexpr int kVec = 4;
   static __device__ __forceinline__ storage neg_inf() { return kNegInf; }
   static __device__ __forceinline__ void unpack(const uint4& w, float (&x)[4]) {

@@ -70,20 +70,36 @@ struct RowVecs {
   __device__ __forceinline__ u32x4 raw(const void* base, int gi) const {
     return __builtin_nontemporal_load(static_cast<const u32x4*>(base) + g0 + gi);
   }
-  // the elements of an edge vector, with -inf outside the row
+  // An edge vector: -inf outside the row, and the array's last vector, which
+  // raw() does not read, element by element.  Whole words through one bit per
+  // element, and a rolled loop: unrolled element loads at every edge site held
+  // 120 registers (of the fp32 passes, 164 against 46 for aligned rows).
   __device__ __forceinline__ u32x4 edge(const void* base, int gi, u32x4 w) const {
     using T = typename TI::storage;
-    T x[E];
-    __builtin_memcpy(x, &w, sizeof w);
+    constexpr int EPW = E / 4, kBits = 32 / EPW;
+    const int i0 = index(gi, 0);
+    const int lo = max(0, -i0), hi = min(E, V - i0);  // the row's elements of the vector
+    if (gi >= nfull) {
+#pragma unroll 1
+      for (int e = lo; e < hi; ++e) {
+        const T x = static_cast<const T*>(base)[(g0 + gi) * E + e];
+        const uint32_t b = EPW == 2 ? uint32_t(__builtin_bit_cast(typename TI::bits, x)) << (e % EPW * 16)
+                                    : uint32_t(__builtin_bit_cast(typename TI::bits, x));
+        const uint32_t keep = e % EPW ? 0xffffu : 0u;  // the word's lower element, written before
 #pragma unroll
-    for (int e = 0; e < E; ++e) {
-      const int i = index(gi, e);
-      if (i < 0 || i >= V)
-        x[e] = TI::neg_inf();
-      else if (gi >= nfull)
-        x[e] = static_cast<const T*>(base)[(g0 + gi) * E + e];
+        for (int q = 0; q < 4; ++q)
+          if (e / EPW == q) w[q] = (w[q] & keep) | b;
+      }
     }
-    __builtin_memcpy(&w, x, sizeof w);
+    const uint32_t in = ((1u << hi) - 1u) & ~((1u << lo) - 1u);
+    const u32x4 out = none();
+#pragma unroll
+    for (int q = 0; q < 4; ++q) {
+      uint32_t m = uint32_t(__builtin_amdgcn_sbfe(int32_t(in), q * EPW, 1));
+      if constexpr (EPW == 2)
+        m = (m & 0xffffu) | (uint32_t(__builtin_amdgcn_sbfe(int32_t(in), q * EPW + 1, 1)) << kBits);
+      w[q] = (w[q] & m) | (out[q] & ~m);
+    }
     return w;
   }
   static __device__ __forceinline__ u32x4 none() {
