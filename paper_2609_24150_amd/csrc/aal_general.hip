@@ -380,6 +380,10 @@ template <class TI, bool VEC, bool NEED_T>
 void rows_launch(const GenArgs& a) {
   if (wide_rows(a.R, a.V))
     rows_blk<TI, VEC, NEED_T, kWideBlock>(a);
+  else if (const int blk = narrow_block(a.V, TI::kVec); blk == kWave)
+    rows_blk<TI, VEC, NEED_T, kWave>(a);
+  else if (blk == 2 * kWave)
+    rows_blk<TI, VEC, NEED_T, 2 * kWave>(a);
   else
     rows_blk<TI, VEC, NEED_T, kBlock>(a);
 }

@@ -19,6 +19,17 @@ constexpr int kWideBlock = 1024;
 // 1024 threads need two rounds of the device, the second half empty).
 static inline bool wide_rows(int64_t rows, int V) { return rows <= 512 && V > 8192; }
 
+// Workgroup size of the same pass for short rows: as many wavefronts as fill
+// four vectors per thread, so that none idles through the row's reductions.
+// Against 256 threads for every short row: WTV over 2000 x 9 rows of 1,501 bf16
+// 159 -> 87 us, forward over 4000 x 7 rows of 2,045 210 -> 112 us, EAL over
+// 3000 x 12 rows of 2,000 162 -> 113 us (two waves for up to 512 vectors: WTV
+// over 3000 x 3 rows of 3,001 107 -> 80 us).
+static inline int narrow_block(int V, int vec) {
+  const int ng = V / vec + 1;
+  return ng <= kWave * 4 ? kWave : ng <= kWave * 8 ? 2 * kWave : kRowBlock;
+}
+
 // Workgroups per row of a pass without a reduction (the gradient passes): as
 // many as bring the launch to 2048 workgroups of 256 threads, eight per CU,
 // each with at least one round of U vectors per thread.

@@ -252,6 +252,10 @@ template <class TI, int MODE, bool VEC>
 hipError_t launch_vec(const LossArgs& a) {
   if (wide_rows(a.N * a.K, a.V))
     stats_launch<TI, MODE, VEC, kWideBlock>(a);
+  else if (const int blk = narrow_block(a.V, TI::kVec); blk == kWave)
+    stats_launch<TI, MODE, VEC, kWave>(a);
+  else if (blk == 2 * kWave)
+    stats_launch<TI, MODE, VEC, 2 * kWave>(a);
   else
     stats_launch<TI, MODE, VEC, kBlock>(a);
   const unsigned wblocks = unsigned((a.N + kBlock - 1) / kBlock);

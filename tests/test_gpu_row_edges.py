@@ -5,7 +5,8 @@ with the tolerances of the entry points' own parity tests.
 The sizes put a row's edges everywhere they can fall: rows shorter than a
 vector, rows whose first and last vectors are the same, a last row that ends
 the allocation inside a vector, more than 8192 entries (wide workgroups) with
-few rows, and 513 rows (the first count that is not wide)."""
+few rows, 513 rows (the first count that is not wide), and the row lengths at
+which a row pass goes from one wavefront to two and to four."""
 import pytest
 import torch
 
@@ -17,7 +18,8 @@ import test_gpu_vp as vp
 pytestmark = pytest.mark.gpu
 
 BF16, F32 = torch.bfloat16, torch.float32
-SHAPES = [(3, 3, 5), (9, 2, 3), (17, 1, 2), (8193, 3, 2), (8200, 2, 2), (20003, 5, 1), (8197, 1, 513)]  # V, K, N
+SHAPES = [(3, 3, 5), (9, 2, 3), (17, 1, 2), (8193, 3, 2), (8200, 2, 2), (20003, 5, 1), (8197, 1, 513),
+          (1023, 2, 3), (1024, 2, 3), (2047, 2, 3), (2048, 2, 3), (4095, 2, 3), (4096, 2, 3)]  # V, K, N
 
 
 @pytest.fixture(scope="module")
