@@ -35,7 +35,7 @@ SIMDS = 1024          # 256 CUs x 4 SIMDs
 CLOCK_HZ = 2.4e9      # MI355X peak engine clock
 HOST_CPU_SHARE = 16
 PMC_PROFILE = os.path.join(ROOT, "profiles", "resident_wtv_c2_pmc.txt")
-KERNEL_SOURCES = ["paper_2609_24150_amd/csrc/aal_resident_loss.h", "paper_2609_24150_amd/csrc/aal_resident_common.h",
+KERNEL_SOURCES = ["paper_2609_24150_amd/csrc/aal_resident.hip", "paper_2609_24150_amd/csrc/aal_resident_common.h",
                   "paper_2609_24150_amd/csrc/aal_device.h", "paper_2609_24150_amd/csrc/aal_internal.h"]
 WORKLOAD_TEXT = {
     "c2": "WTV fwd+bwd: N=2048 windows x K=7 x V=128256, bf16 logits, bf16 grad, T=1.0/1.0",

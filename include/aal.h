@@ -132,10 +132,10 @@ const char* aal_last_error(void);
  *                     upstream dL/dloss), or NULL for 1.0.  Not applied to loss.
  * workspace         : at least aal_workspace_bytes(N*K, N) bytes, 256-byte aligned.
  * The default schedule is one register-resident kernel when V is a multiple
- * of 8 (bf16) / 4 (fp32) elements, K is at most 16 and a window fits the
- * co-resident grid; every other shape, and some calls with K of 9 to 15 for
- * which it is faster, take the multi-kernel streaming schedule.  A poll
- * time-out of the resident schedule (not expected) sets the loss to NaN.
+ * of 8 (bf16) / 4 (fp32) elements, K is in {1..8, 16} and a window fits the
+ * co-resident grid; every other shape takes the multi-kernel streaming
+ * schedule.  A poll time-out of the resident schedule (not expected) sets
+ * the loss to NaN.
  */
 aal_status_t aal_eal_fwd_bwd(const void* z_draft, const void* z_target, aal_dtype_t in_dtype,
                              int64_t N, int32_t K, int32_t V, float temp_draft,
@@ -316,9 +316,8 @@ size_t aal_loss_workspace_bytes(aal_layout_t layout, int64_t B, int32_t S, int32
  * grad_draft, grad_dtype, grad_scale : as for aal_eal_fwd_bwd.
  * flags   : AAL_FLAG_* bits.  By default one register-resident kernel reads each
  *           logit once and writes the gradient once when V is a multiple of 8
- *           (bf16) / 4 (fp32), K is at most 16 and z_target is given; other
- *           shapes, forward-only or AAL_FLAG_COOPERATIVE calls with K of 9 to 15, and
- *           AAL_FLAG_STREAMING, take the multi-kernel schedule.
+ *           (bf16) / 4 (fp32), K is in {1..8, 16} and z_target is given; other
+ *           shapes, and AAL_FLAG_STREAMING, take the multi-kernel schedule.
  *           AAL_FLAG_COOPERATIVE: see "Concurrency".  A poll time-out of the
  *           resident schedule (not expected) sets the loss to NaN.
  * workspace : at least aal_loss_workspace_bytes(layout, B, S, K) bytes.

@@ -456,14 +456,7 @@ hipError_t launch_general_resident(const GenArgs& a, bool* used) {
   *used = false;
   const int E = a.in == DType::kBf16 ? Bf16::kVec : F32::kVec;
   if (a.V % E != 0 || a.zt == nullptr || a.res_slots == nullptr) return hipSuccess;
-  const bool lng = a.K > 8;
-  if (a.in == DType::kBf16) {
-    if (a.gd == DType::kF32)
-      return lng ? launch_general_resident_bf16_g32_long(a, used) : launch_general_resident_bf16_g32(a, used);
-    return lng ? launch_general_resident_bf16_long(a, used) : launch_general_resident_bf16(a, used);
-  }
-  if (a.gd != DType::kF32) return hipSuccess;  // fp32 logits with a bf16 gradient: streaming schedule
-  return lng ? launch_general_resident_f32_long(a, used) : launch_general_resident_f32(a, used);
+  return a.in == DType::kBf16 ? launch_general_resident_bf16(a, used) : launch_general_resident_f32(a, used);
 }
 
 hipError_t launch_general(const GenArgs& a) {

@@ -87,11 +87,10 @@ hipError_t launch_streaming(const LossArgs& a);
 hipError_t launch_loss_reduce(const LossArgs& a, const unsigned* err = nullptr);
 
 // Register-resident single-kernel schedule.  Sets *used = false (and enqueues
-// nothing) when the shape is outside what it supports: V not a multiple of
-// the 16-byte vector, K above 16, a window too wide for the co-resident grid,
-// or (with a.coop) no cooperative launch on the device.
+// nothing) when the shape is outside what it supports: V not a multiple of the 16-byte vector, K outside {1..8, 16}, a window too
+// wide for the co-resident grid, or (with a.coop) no cooperative launch on
+// the device.
 hipError_t launch_resident(const LossArgs& a, bool* used);
-hipError_t launch_resident_f32(const LossArgs& a, bool* used);  // fp32 logits
 
 // Per-row statistics of the combined-objective schedule.  64 bytes.
 struct GenStats {
@@ -157,7 +156,7 @@ struct GenArgs {
 };
 
 // The combined objective: the register-resident schedule when the shape
-// allows it (V a multiple of the 16-byte vector, K up to 16, target
+// allows it (V a multiple of the 16-byte vector, K in {1..8, 16}, target
 // logits given, cooperative launch), else the row pass, window scan, loss and
 // gradient pass of the streaming schedule, which handles every shape.
 hipError_t launch_general(const GenArgs& a);
@@ -166,14 +165,9 @@ hipError_t launch_general(const GenArgs& a);
 // (enqueuing nothing) when the shape is outside what it supports.  The loss
 // reduction and the time-out check are left to the caller.
 hipError_t launch_general_resident(const GenArgs& a, bool* used);
-// Its instances by logit type, gradient type and window length (up to 8, and
-// 9 to 16), each set compiled in its own file.
-hipError_t launch_general_resident_bf16(const GenArgs& a, bool* used);
-hipError_t launch_general_resident_bf16_long(const GenArgs& a, bool* used);
-hipError_t launch_general_resident_bf16_g32(const GenArgs& a, bool* used);
-hipError_t launch_general_resident_bf16_g32_long(const GenArgs& a, bool* used);
-hipError_t launch_general_resident_f32(const GenArgs& a, bool* used);
-hipError_t launch_general_resident_f32_long(const GenArgs& a, bool* used);
+hipError_t launch_general_resident_bf16(const GenArgs& a, bool* used);  // bf16 logits
+hipError_t launch_general_resident_bf16_g32(const GenArgs& a, bool* used);  // bf16 logits, fp32 gradient
+hipError_t launch_general_resident_f32(const GenArgs& a, bool* used);   // fp32 logits
 // Loss reduction of the combined objective over the per-row and per-window
 // values in the workspace.
 // err: the error word of the resident kernel (NaN loss when set), or null

@@ -44,8 +44,6 @@
 // Polls are bounded (a timeout sets an error word and the loss becomes NaN;
 // the kernel always exits).  With a multiple of 8 teams, team members share
 // blockIdx % 8, i.e. one XCD; otherwise they span XCDs.
-#pragma once
-
 #include "aal_device.h"
 #include "aal_internal.h"
 #include "aal_resident_common.h"
@@ -1014,26 +1012,11 @@ hipError_t launch_k(const LossArgs& a, bool* used) {
   const int64_t grow_bytes = int64_t(a.V) * (a.gd == DType::kBf16 ? 2 : 4);
   if (int64_t(K) * grow_bytes >= (int64_t(1) << 31) || int64_t(K) * row_bytes >= (int64_t(1) << 31))
     return hipSuccess;  // 32-bit in-window offsets
-  // Window lengths 9 to 15 keep one vector per row and thread, so the team
-  // exchanges of a window (two to three microseconds each) cover less
-  // arithmetic than at K <= 8, and the streaming schedule is the better one
-  //   without a gradient (WTV over 256 x 10 rows of 65,536 bf16: 217 us
-  //     against 264 us here; with one, 512 x 9 rows: 719 against 487 us here);
-  //   for EAL, which streaming reads in one sweep, over short rows (600 x 10
-  //     rows of 12,000 bf16: 116 against 123 us; 512 x 14 rows of 32,000: 333
-  //     against 300 us here).
-  // Calls with a.coop also stay with it: no wait between workgroups, and no
-  // need of a cooperative launch.
-  constexpr bool kMid = K > 8 && K < 16;
-  if (kMid && (a.coop || a.grad == nullptr || (MODE == int(Mode::kEal) && row_bytes < 48 * 1024))) return hipSuccess;
   int per_cu = 0;
   hipError_t e = hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, kern, kBlock, 0);
   if (e != hipSuccess) return e;
   const int64_t resident = int64_t(per_cu) * di.cus;
   int64_t T = resident / W;
-  // ... and for one window per single-workgroup team (WTV over 64 x 13 rows of
-  // 2,048: 22 us against 26 us here; 2000 x 13 rows: 215 against 159 us here).
-  if (kMid && W == 1 && a.N <= T) return hipSuccess;
   // every co-resident team runs; with a multiple of 8 teams the members of a
   // team share an XCD, otherwise they span XCDs (measured: no slower than the
   // XCD-local exchange, and rounding the team count down idled up to 19% of
@@ -1090,13 +1073,6 @@ hipError_t launch_mode(const LossArgs& a, bool* used) {
     case 6: return launch_k<TI, TG, MODE, 6>(a, used);
     case 7: return launch_k<TI, TG, MODE, 7>(a, used);
     case 8: return launch_k<TI, TG, MODE, 8>(a, used);
-    case 9: return launch_k<TI, TG, MODE, 9>(a, used);
-    case 10: return launch_k<TI, TG, MODE, 10>(a, used);
-    case 11: return launch_k<TI, TG, MODE, 11>(a, used);
-    case 12: return launch_k<TI, TG, MODE, 12>(a, used);
-    case 13: return launch_k<TI, TG, MODE, 13>(a, used);
-    case 14: return launch_k<TI, TG, MODE, 14>(a, used);
-    case 15: return launch_k<TI, TG, MODE, 15>(a, used);
     case 16: return launch_k<TI, TG, MODE, 16>(a, used);
     default: return hipSuccess;
   }
@@ -1111,4 +1087,12 @@ hipError_t launch_in(const LossArgs& a, bool* used) {
 }
 
 }  // namespace
+
+hipError_t launch_resident(const LossArgs& a, bool* used) {
+  *used = false;
+  const int E = a.in == DType::kBf16 ? Bf16::kVec : F32::kVec;
+  if (a.V % E != 0) return hipSuccess;
+  return a.in == DType::kBf16 ? launch_in<Bf16>(a, used) : launch_in<F32>(a, used);
+}
+
 }  // namespace aal

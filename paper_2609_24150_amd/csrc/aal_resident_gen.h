@@ -1193,14 +1193,6 @@ hipError_t launch_kg(const GenArgs& a, bool* used) {
   const int64_t grow_bytes = int64_t(a.V) * (a.gd == DType::kBf16 ? 2 : 4);
   if (int64_t(K) * grow_bytes >= (int64_t(1) << 31) || int64_t(K) * row_bytes >= (int64_t(1) << 31))
     return hipSuccess;
-  // Window lengths 9 to 15 keep one vector per row and thread; without a
-  // gradient the streaming schedule is then faster, as for the WTV loss (see
-  // aal_resident_loss.h).  With one: KL + TV over 4 x 512 rows of 32,000 bf16,
-  // K = 10, 199 us streaming against 167 us here; WTV over 1000 x 10 rows of
-  // 4,096 141 against 92 us; KL + EAL over 2 x 900 rows of 65,536, K = 12,
-  // 340 against 268 us.  Calls with a.coop also stay with it: no wait between
-  // workgroups, and no need of a cooperative launch.
-  if (K > 8 && K < 16 && (a.coop || a.grad == nullptr)) return hipSuccess;
   const int S = a.layout == 0 ? K : a.S;
   const int CS = (S + K - 1) / K;
   const int64_t NC = a.B * CS;
@@ -1274,33 +1266,40 @@ hipError_t launch_kg(const GenArgs& a, bool* used) {
   return hipSuccess;
 }
 
-// K0 .. K0 + 7
-template <class TI, class TG, int K0, int VAR>
+template <class TI, class TG, int VAR>
 hipError_t launch_kl(const GenArgs& a, bool* used) {
-  switch (a.K - K0) {
-    case 0: return launch_kg<TI, TG, K0 + 0, VAR>(a, used);
-    case 1: return launch_kg<TI, TG, K0 + 1, VAR>(a, used);
-    case 2: return launch_kg<TI, TG, K0 + 2, VAR>(a, used);
-    case 3: return launch_kg<TI, TG, K0 + 3, VAR>(a, used);
-    case 4: return launch_kg<TI, TG, K0 + 4, VAR>(a, used);
-    case 5: return launch_kg<TI, TG, K0 + 5, VAR>(a, used);
-    case 6: return launch_kg<TI, TG, K0 + 6, VAR>(a, used);
-    case 7: return launch_kg<TI, TG, K0 + 7, VAR>(a, used);
+  switch (a.K) {
+    case 1: return launch_kg<TI, TG, 1, VAR>(a, used);
+    case 2: return launch_kg<TI, TG, 2, VAR>(a, used);
+    case 3: return launch_kg<TI, TG, 3, VAR>(a, used);
+    case 4: return launch_kg<TI, TG, 4, VAR>(a, used);
+    case 5: return launch_kg<TI, TG, 5, VAR>(a, used);
+    case 6: return launch_kg<TI, TG, 6, VAR>(a, used);
+    case 7: return launch_kg<TI, TG, 7, VAR>(a, used);
+    case 8: return launch_kg<TI, TG, 8, VAR>(a, used);
+    case 16: return launch_kg<TI, TG, 16, VAR>(a, used);
     default: return hipSuccess;
   }
 }
 
-template <class TI, class TG, int K0>
+template <class TI, class TG>
 hipError_t launch_tg(const GenArgs& a, bool* used) {
   // sum min(p, q) is needed by the WTV and TV terms and by the a_tv / E_tv
   // outputs (which the KL term alone would otherwise leave unevaluated)
   const bool tv = a.w_wtv != 0.f || a.w_tv != 0.f || (a.w_kl != 0.f && (a.accept_tv || a.e_tv));
   const bool kl = a.w_kl != 0.f;
   const bool am = a.w_eal != 0.f && a.labels == nullptr;
-  if (!tv && !kl) return am ? launch_kl<TI, TG, K0, 4>(a, used) : hipSuccess;  // EAL with labels: streaming
-  if (kl && tv) return am ? launch_kl<TI, TG, K0, 15>(a, used) : launch_kl<TI, TG, K0, 11>(a, used);
-  if (kl) return am ? launch_kl<TI, TG, K0, 7>(a, used) : launch_kl<TI, TG, K0, 3>(a, used);
-  return am ? launch_kl<TI, TG, K0, 13>(a, used) : launch_kl<TI, TG, K0, 9>(a, used);
+  if (!tv && !kl) return am ? launch_kl<TI, TG, 4>(a, used) : hipSuccess;  // EAL with labels: streaming
+  if (kl && tv) return am ? launch_kl<TI, TG, 15>(a, used) : launch_kl<TI, TG, 11>(a, used);
+  if (kl) return am ? launch_kl<TI, TG, 7>(a, used) : launch_kl<TI, TG, 3>(a, used);
+  return am ? launch_kl<TI, TG, 13>(a, used) : launch_kl<TI, TG, 9>(a, used);
+}
+
+template <class TI>
+hipError_t launch_ti(const GenArgs& a, bool* used) {
+  if (a.gd == DType::kF32) return launch_tg<TI, GF32>(a, used);
+  if constexpr (std::is_same_v<TI, Bf16>) return launch_tg<TI, GBf16>(a, used);
+  return hipSuccess;  // fp32 logits with a bf16 gradient: streaming schedule
 }
 
 }  // namespace

@@ -1,8 +1,12 @@
-"""The register-resident schedules at window lengths 9 to 15 (one vector per
-row and thread; at 10 and above part of a window is not staged in LDS),
-against the fp64 oracle with the tolerances of the entry points' own parity
-tests: several windows per team, teams of several members with a ragged last
-one, sequences whose last chunk is short."""
+"""Window lengths 9 to 15, which take the streaming schedule in every form of
+a call: against the fp64 oracle with the tolerances of the entry points' own
+parity tests (EAL gradients: widened by a bound on K rounded acceptances);
+and the properties that callers get from one schedule for all forms: the same
+bits whichever flag is set and whether or not a gradient is asked for, and no
+waits between workgroups, so that calls on several streams hold nothing from
+each other."""
+import math
+
 import pytest
 import torch
 
@@ -28,10 +32,8 @@ def A():
 @pytest.mark.parametrize("K", range(9, 16))
 def test_losses(A, K, dtype, gdtype):
     dev = torch.device("cuda:0")
-    # WTV: 3 (bf16) or 5 (fp32) members per team, the last one ragged; 85 or 51 teams
     zd, zt = parity_cases._inputs("c1" if dtype == F32 else "c2", (100, K, 8808), dtype, seed=K, dev=dev)
     parity_cases._check_wtv(A, zd, zt, 0.9, 1.1, gdtype, 0)
-    # EAL: 6 or 12 members (shorter rows take the streaming schedule); 42 or 21 teams.
     # A row's coefficient multiplies up to K acceptances q(x*) = 2^(z sc - msc - l2s); the
     # exponent's two roundings (|msc|, |l2s| < 32: half a unit is 2^-20 each, times ln 2) put up to
     # 1.4 * 2^-20 of relative error on each, so K of them exceed the 2^-18 of check_grad from K = 3 on.
@@ -56,3 +58,49 @@ def test_combined(A, K, weights, dtype, gdtype):
     zd, zt = general._inputs(2, 3 * K + 4, 8808, dtype, seed=K)
     general._check(A, zd, zt, K, weights, general.SEQ, Td=0.8, Tt=1.2, gdt=gdtype)
     general._check(A, zd[:, :K].contiguous(), zt[:, :K].contiguous(), K, weights, general.WIN, gdt=gdtype)
+
+
+def _calls(A, K, dev):
+    """The loss calls at window length K, over shapes whose rows span several workgroups' worth of
+    vectors; each takes grad and flags."""
+    zd, zt = parity_cases._inputs("c2", (60, K, 24584), BF16, seed=K, dev=dev)
+    fd, ft = parity_cases._inputs("c1", (30, K, 8808), F32, seed=K, dev=dev)
+    sd, st = parity_cases._inputs("c2", (2, 3 * K + 4, 8808), BF16, seed=K, dev=dev)
+    calls = {
+        "eal": lambda **kw: A.aal_eal_fwd_bwd(zd, zt, 0.9, **kw),
+        "wtv": lambda **kw: A.aal_wtv_fwd_bwd(zd, zt, 0.9, 1.1, **kw),
+        "wtv fp32": lambda **kw: A.aal_wtv_fwd_bwd(fd, ft, 0.9, 1.1, **kw),
+        "wtv, fp32 gradient": lambda **kw: A.aal_wtv_fwd_bwd(zd, zt, 0.9, 1.1, grad_dtype=F32, **kw),
+    }
+    for weights in general.WEIGHTS:
+        calls[f"windows {weights}"] = lambda w=weights, **kw: A.aal_loss_fwd_bwd(zd, zt, K, weights=w, **kw)
+        calls[f"sequences {weights}"] = lambda w=weights, **kw: A.aal_loss_fwd_bwd(
+            sd, st, K, weights=w, layout=A.AAL_LAYOUT_SEQUENCES, **kw)
+    return calls
+
+
+@pytest.mark.parametrize("K", range(9, 16))
+def test_same_bits_in_every_form(A, K):
+    dev = torch.device("cuda:0")
+    for name, call in _calls(A, K, dev).items():
+        ref = call(grad=True, flags=0)
+        forms = {"cooperative": call(grad=True, flags=A.AAL_FLAG_COOPERATIVE),
+                 "streaming": call(grad=True, flags=A.AAL_FLAG_STREAMING),
+                 "forward only": call(grad=False, flags=0)}
+        torch.cuda.synchronize()
+        for form, r in forms.items():
+            for k, v in ref.items():
+                if v is not None and not (k == "grad" and form == "forward only"):
+                    assert torch.equal(r[k].view(torch.uint8), v.view(torch.uint8)), (name, form, k)
+
+
+@pytest.mark.parametrize("K", range(9, 16))
+def test_no_waits_between_workgroups(A, K, monkeypatch):
+    """A schedule whose workgroups wait for each other reads NaN when it is started in its timed-out
+    state (see test_gpu_timeout); these calls have no such state."""
+    calls = _calls(A, K, torch.device("cuda:0"))
+    monkeypatch.setenv("AAL_TEST_PRESET_TIMEOUT", "1")
+    for name, call in calls.items():
+        r = call(grad=True, flags=0)
+        torch.cuda.synchronize()
+        assert math.isfinite(r["loss"].item()), name
