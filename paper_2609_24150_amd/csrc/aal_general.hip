@@ -60,34 +60,10 @@ __global__ __launch_bounds__(BLK) void k_gen_rows(const void* __restrict__ zd, c
       rv.load({zd}, base, BLK, w);
       rv.unpack(w[0], xd);
     }
-    float cm = kNegInf;
-#pragma unroll
-    for (int u = 0; u < U; ++u)
-#pragma unroll
-      for (int e = 0; e < E; ++e) cm = fmaxf(cm, xd[u][e]);
-    if (lse_rebase(sd, cm, scd)) {
-      float acc = 0.f;
-#pragma unroll
-      for (int u = 0; u < U; ++u)
-#pragma unroll
-        for (int e = 0; e < E; ++e) acc += ex2(__builtin_fmaf(xd[u][e], scd, -sd.msc));
-      sd.s += acc;
-    }
+    lse_fold(sd, xd, scd);
     if constexpr (NEED_T) {
       if (want_pq) {
-        float ct = kNegInf;
-#pragma unroll
-        for (int u = 0; u < U; ++u)
-#pragma unroll
-          for (int e = 0; e < E; ++e) ct = fmaxf(ct, xt[u][e]);
-        if (lse_rebase(st, ct, sct)) {
-          float acc = 0.f;
-#pragma unroll
-          for (int u = 0; u < U; ++u)
-#pragma unroll
-            for (int e = 0; e < E; ++e) acc += ex2(__builtin_fmaf(xt[u][e], sct, -st.msc));
-          st.s += acc;
-        }
+        lse_fold(st, xt, sct);
       }
       if (argmax) {
 #pragma unroll
@@ -130,24 +106,30 @@ __global__ __launch_bounds__(BLK) void k_gen_rows(const void* __restrict__ zd, c
       rv.load({zd, zt}, base, BLK, w);
       rv.unpack(w[0], xd);
       rv.unpack(w[1], xt);
-      float am = 0.f, aq = 0.f, ak = 0.f;
+      float am[U], aq[U], ak[U];
 #pragma unroll
-      for (int u = 0; u < U; ++u)
+      for (int u = 0; u < U; ++u) {
+        float vm[E], vq[E], vk[E];
 #pragma unroll
         for (int e = 0; e < E; ++e) {
           const float ld = __builtin_fmaf(xd[u][e], scd, -sd.msc) - l2sd;  // log2 q
           const float lt = __builtin_fmaf(xt[u][e], sct, -st.msc) - l2st;  // log2 p
           const float m = ex2(fminf(ld, lt));
-          am += m;
-          aq += (ld < lt) ? m : 0.f;
+          vm[e] = m;
+          vq[e] = (ld < lt) ? m : 0.f;
+          vk[e] = 0.f;
           if (want_kl) {
             const float pv = ex2(lt);
-            ak += (pv > 0.f) ? pv * (lt - ld) : 0.f;  // p = 0 (masked) contributes nothing
+            vk[e] = (pv > 0.f) ? pv * (lt - ld) : 0.f;  // p = 0 (masked) contributes nothing
           }
         }
-      smin += am;
-      qlt += aq;
-      kl += ak;
+        am[u] = tree_sum(vm);
+        aq[u] = tree_sum(vq);
+        ak[u] = tree_sum(vk);
+      }
+      smin += tree_sum(am);
+      qlt += tree_sum(aq);
+      kl += tree_sum(ak);
     }
     smin = block_sum<BLK / kWave>(smin, sh_f);
     qlt = block_sum<BLK / kWave>(qlt, sh_f);

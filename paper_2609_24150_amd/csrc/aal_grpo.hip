@@ -60,13 +60,10 @@ __global__ __launch_bounds__(BLK) void k_grpo_rows(const void* __restrict__ zth,
       rv.unpack(w[0], xa);
       rv.unpack(w[1], xb);
     }
-    float ca = kNegInf, cb = kNegInf;
 #pragma unroll
     for (int u = 0; u < U; ++u)
 #pragma unroll
       for (int e = 0; e < E; ++e) {
-        ca = fmaxf(ca, xa[u][e]);
-        cb = fmaxf(cb, xb[u][e]);
         const int idx = rv.index(base + u * BLK, e);
         if (xa[u][e] > bth) { bth = xa[u][e]; ith = idx; }
         if (xb[u][e] > brf) { brf = xb[u][e]; irf = idx; }
@@ -74,22 +71,8 @@ __global__ __launch_bounds__(BLK) void k_grpo_rows(const void* __restrict__ zth,
           if (xc[u][e] > bt) { bt = xc[u][e]; it = idx; }
         }
       }
-    if (lse_rebase(sth, ca, sc)) {
-      float acc = 0.f;
-#pragma unroll
-      for (int u = 0; u < U; ++u)
-#pragma unroll
-        for (int e = 0; e < E; ++e) acc += ex2(__builtin_fmaf(xa[u][e], sc, -sth.msc));
-      sth.s += acc;
-    }
-    if (lse_rebase(srf, cb, sc)) {
-      float acc = 0.f;
-#pragma unroll
-      for (int u = 0; u < U; ++u)
-#pragma unroll
-        for (int e = 0; e < E; ++e) acc += ex2(__builtin_fmaf(xb[u][e], sc, -srf.msc));
-      srf.s += acc;
-    }
+    lse_fold(sth, xa, sc);
+    lse_fold(srf, xb, sc);
   }
   sth = block_lse<BLK / kWave>(sth, sc, sh_lse);
   srf = block_lse<BLK / kWave>(srf, sc, sh_lse);

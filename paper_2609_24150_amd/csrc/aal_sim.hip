@@ -76,30 +76,10 @@ __global__ __launch_bounds__(BLK) void k_sim_rows(const void* __restrict__ zd, c
     }
     if (lane == 0) tile_stat[t] = make_float2(tmsc, tsum);
 
-    float ct = kNegInf;
-#pragma unroll
-    for (int u = 0; u < U; ++u)
-#pragma unroll
-      for (int e = 0; e < E; ++e) ct = fmaxf(ct, xt[u][e]);
-    if (lse_rebase(st, ct, sc)) {
-      float acc = 0.f;
-#pragma unroll
-      for (int u = 0; u < U; ++u)
-#pragma unroll
-        for (int e = 0; e < E; ++e) acc += ex2(__builtin_fmaf(xt[u][e], sc, -st.msc));
-      st.s += acc;
-    }
+    lse_fold(st, xt, sc);
   }
   __syncthreads();
-  // target normaliser (block-wide, deterministic order)
-  {
-    LseState ws = wave_lse(st, sc);
-    if (lane == 0) sh_lse[w] = ws;
-    __syncthreads();
-    st = sh_lse[0];
-#pragma unroll
-    for (int i = 1; i < BLK / kWave; ++i) st = lse_merge(st, sh_lse[i], sc);
-  }
+  st = block_lse<BLK / kWave>(st, sc, sh_lse);  // the target's normaliser
 
   // Wave 0: locate the tile whose cumulative draft mass crosses u1 * total.
   if (w == 0) {

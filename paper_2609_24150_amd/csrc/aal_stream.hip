@@ -49,33 +49,9 @@ __global__ __launch_bounds__(BLK) void k_row_stats(const void* __restrict__ zd, 
     rv.load({zd, zt}, base, BLK, w);
     rv.unpack(w[0], xd);
     rv.unpack(w[1], xt);
-    float cm = kNegInf;
-#pragma unroll
-    for (int u = 0; u < U; ++u)
-#pragma unroll
-      for (int e = 0; e < E; ++e) cm = fmaxf(cm, xd[u][e]);
-    if (lse_rebase(sd, cm, scd)) {
-      float acc = 0.f;
-#pragma unroll
-      for (int u = 0; u < U; ++u)
-#pragma unroll
-        for (int e = 0; e < E; ++e) acc += ex2(__builtin_fmaf(xd[u][e], scd, -sd.msc));
-      sd.s += acc;
-    }
+    lse_fold(sd, xd, scd);
     if constexpr (MODE == int(Mode::kWtv)) {
-      float ct = kNegInf;
-#pragma unroll
-      for (int u = 0; u < U; ++u)
-#pragma unroll
-        for (int e = 0; e < E; ++e) ct = fmaxf(ct, xt[u][e]);
-      if (lse_rebase(st, ct, sct)) {
-        float acc = 0.f;
-#pragma unroll
-        for (int u = 0; u < U; ++u)
-#pragma unroll
-          for (int e = 0; e < E; ++e) acc += ex2(__builtin_fmaf(xt[u][e], sct, -st.msc));
-        st.s += acc;
-      }
+      lse_fold(st, xt, sct);
     } else {
 #pragma unroll
       for (int u = 0; u < U; ++u)
@@ -113,19 +89,23 @@ __global__ __launch_bounds__(BLK) void k_row_stats(const void* __restrict__ zd, 
       rv.load({zd, zt}, base, BLK, w);
       rv.unpack(w[0], xd);
       rv.unpack(w[1], xt);
-      float am = 0.f, aq = 0.f;
+      float am[U], aq[U];
 #pragma unroll
-      for (int u = 0; u < U; ++u)
+      for (int u = 0; u < U; ++u) {
+        float vm[E], vq[E];
 #pragma unroll
         for (int e = 0; e < E; ++e) {
           const float ld = __builtin_fmaf(xd[u][e], scd, -sd.msc) - l2sd;
           const float lt = __builtin_fmaf(xt[u][e], sct, -st.msc) - l2st;
           const float m = ex2(fminf(ld, lt));
-          am += m;
-          aq += (ld < lt) ? m : 0.f;
+          vm[e] = m;
+          vq[e] = (ld < lt) ? m : 0.f;
         }
-      smin += am;
-      qlt += aq;
+        am[u] = tree_sum(vm);
+        aq[u] = tree_sum(vq);
+      }
+      smin += tree_sum(am);
+      qlt += tree_sum(aq);
     }
     smin = block_sum<BLK / kWave>(smin, sh_f);
     qlt = block_sum<BLK / kWave>(qlt, sh_f);
