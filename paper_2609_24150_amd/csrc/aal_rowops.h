@@ -45,32 +45,41 @@ static inline unsigned row_splits(int64_t rows, int V, int vec, int U) {
 // are 16-byte aligned and share the element index, so a row has the same
 // phase in each of them): its first and last vectors are shared with the
 // neighbouring rows and are loaded whole like the others, then the elements
-// outside the row become -inf.  Only the array's very last vector, which may
-// reach past the allocation, is read element by element, and the stores at a
-// row's edges go element by element.  Against element-by-element accesses of
+// outside the row become -inf.  Only the array's very last vector may reach
+// past the allocation: in its place the array's last 16 bytes are loaded, by
+// the same instruction, and moved to where they belong (an array of less than
+// 16 bytes is read element by element).  The stores at a row's edges go
+// element by element.  Against element-by-element accesses of
 // the whole row: the simulation over 447,252 rows of 2,587 bf16 logits 4.12 ->
 // 1.51 ms, the KL + TV passes over 768 rows of 50,001 145 + 77 -> 83 + 47 us,
 // the WTV passes over 1792 rows of 32,001 117 + 75 -> 94 + 70 us.
+typedef u32x4 u32x4_any __attribute__((aligned(2)));  // a vector at any element
+
 template <class TI, bool ALIGNED>
 struct RowVecs {
   static constexpr int E = TI::kVec;
   int64_t g0;  // vector index of the row's first vector
   int ng;      // vectors that cover the row
   int nfull;   // of them, those that lie inside the array
+  int nload;   // and those that raw() reads: all, unless the array is shorter than a vector
+  int last;    // element past g0 * E at which the array's last 16 bytes start
   int head;    // elements of the first vector before the row
   int V;
 
   __device__ __forceinline__ RowVecs(int64_t row, int64_t rows, int v) : V(v) {
     if constexpr (ALIGNED) {
-      nfull = ng = v / E;
+      nload = nfull = ng = v / E;
       g0 = row * int64_t(ng);
-      head = 0;
+      head = last = 0;
     } else {
       const int64_t e0 = row * int64_t(v);
       g0 = e0 / E;
       head = int(e0 - g0 * E);
       ng = int((int64_t(head) + v + E - 1) / E);
-      nfull = int(min(int64_t(ng), rows * v / E - g0));
+      const int64_t end = rows * v - g0 * E;  // the array's, from the row's first vector on
+      nfull = int(min(int64_t(ng), end / E));
+      nload = rows * v >= E ? ng : 0;
+      last = int(min(end - E, int64_t(INT_MAX)));
     }
   }
   // index in the row of element e of vector gi (outside [0, V) at the edges)
@@ -78,19 +87,27 @@ struct RowVecs {
   __device__ __forceinline__ bool whole(int gi) const {
     return ALIGNED || (index(gi, 0) >= 0 && index(gi, 0) <= V - E);
   }
+  // the vector's 16 bytes, or the array's last 16 if it reaches past them
   __device__ __forceinline__ u32x4 raw(const void* base, int gi) const {
-    return __builtin_nontemporal_load(static_cast<const u32x4*>(base) + g0 + gi);
+    if constexpr (ALIGNED) {
+      return __builtin_nontemporal_load(static_cast<const u32x4*>(base) + g0 + gi);
+    } else {
+      const typename TI::storage* p = static_cast<const typename TI::storage*>(base) + g0 * E;
+      return __builtin_nontemporal_load(reinterpret_cast<const u32x4_any*>(p + min(gi * E, last)));
+    }
   }
-  // An edge vector: -inf outside the row, and the array's last vector, which
-  // raw() does not read, element by element.  Whole words through one bit per
-  // element, and a rolled loop: unrolled element loads at every edge site held
-  // 120 registers (of the fp32 passes, 164 against 46 for aligned rows).
+  // An edge vector of which raw() gave w: moved to its place where it is the
+  // array's last, and -inf outside the row, by whole words through one bit per
+  // element.  Unrolled element loads at every edge site held 120 registers (of
+  // the fp32 passes, 164 against 46 for aligned rows); a rolled loop over them,
+  // each load waited for, cost small calls a round trip per element (the row
+  // pass over 300 rows of 5,003 bf16: 10.0 us against 7.9).
   __device__ __forceinline__ u32x4 edge(const void* base, int gi, u32x4 w) const {
     using T = typename TI::storage;
     constexpr int EPW = E / 4, kBits = 32 / EPW;
     const int i0 = index(gi, 0);
     const int lo = max(0, -i0), hi = min(E, V - i0);  // the row's elements of the vector
-    if (gi >= nfull) {
+    if (gi >= nload) {
 #pragma unroll 1
       for (int e = lo; e < hi; ++e) {
         const T x = static_cast<const T*>(base)[(g0 + gi) * E + e];
@@ -100,6 +117,17 @@ struct RowVecs {
 #pragma unroll
         for (int q = 0; q < 4; ++q)
           if (e / EPW == q) w[q] = (w[q] & keep) | b;
+      }
+    } else if (gi >= nfull) {
+      // w starts at element `last` and the vector at gi * E: down by the difference
+      const int by = gi * E - last, words = by / EPW;
+#pragma unroll
+      for (int k = 2; k > 0; k /= 2)
+#pragma unroll
+        for (int q = 0; q < 4; ++q) w[q] = words & k ? (q + k < 4 ? w[q + k] : 0u) : w[q];
+      if constexpr (EPW == 2) {
+#pragma unroll
+        for (int q = 0; q < 4; ++q) w[q] = __builtin_amdgcn_alignbit(q < 3 ? w[q + 1] : 0u, w[q], by % EPW * kBits);
       }
     }
     const uint32_t in = ((1u << hi) - 1u) & ~((1u << lo) - 1u);
@@ -124,7 +152,7 @@ struct RowVecs {
   // vector gi, -inf outside the row
   __device__ __forceinline__ u32x4 load(const void* base, int gi) const {
     u32x4 w = none();
-    if (gi < nfull) w = raw(base, gi);
+    if (gi < nload) w = raw(base, gi);
     if (!whole(gi) && gi < ng) w = edge(base, gi, w);
     return w;
   }
@@ -135,7 +163,7 @@ struct RowVecs {
 #pragma unroll
     for (int u = 0; u < U; ++u) {
       const int gi = base + u * step;
-      if (gi < nfull) {
+      if (gi < nload) {
 #pragma unroll
         for (int n = 0; n < N; ++n) w[n][u] = raw(p[n], gi);
       } else {

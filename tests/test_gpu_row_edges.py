@@ -19,7 +19,9 @@ pytestmark = pytest.mark.gpu
 
 BF16, F32 = torch.bfloat16, torch.float32
 SHAPES = [(3, 3, 5), (9, 2, 3), (17, 1, 2), (8193, 3, 2), (8200, 2, 2), (20003, 5, 1), (8197, 1, 513),
-          (1023, 2, 3), (1024, 2, 3), (2047, 2, 3), (2048, 2, 3), (4095, 2, 3), (4096, 2, 3)]  # V, K, N
+          (1023, 2, 3), (1024, 2, 3), (2047, 2, 3), (2048, 2, 3), (4095, 2, 3), (4096, 2, 3),
+          # arrays that end 1, 3 and 4 elements into a vector (and 2, 5, 6, 7 above), arrays shorter than one
+          (5, 1, 5), (11, 3, 3), (3, 1, 4), (3, 1, 2), (1, 1, 3)]  # V, K, N
 
 
 @pytest.fixture(scope="module")
