@@ -351,33 +351,24 @@ __global__ __launch_bounds__(kBlock) void k_gen_grad(const void* __restrict__ zd
   }
 }
 
-template <class TI, bool VEC, bool NEED_T, int BLK>
-void rows_blk(const GenArgs& a) {
-  k_gen_rows<TI, VEC, 4, NEED_T, BLK><<<dim3(unsigned(a.R)), BLK, 0, a.stream>>>(
-      a.zd, a.zt, a.labels, a.V, a.sc_d, a.sc_t, a.w_eal != 0.f, a.w_wtv != 0.f || a.w_tv != 0.f || a.w_kl != 0.f,
-      a.w_kl != 0.f, a.stats);
-}
-
 template <class TI, bool VEC, bool NEED_T>
 void rows_launch(const GenArgs& a) {
-  if (wide_rows(a.R, a.V))
-    rows_blk<TI, VEC, NEED_T, kWideBlock>(a);
-  else if (const int blk = narrow_block(a.V, TI::kVec); blk == kWave)
-    rows_blk<TI, VEC, NEED_T, kWave>(a);
-  else if (blk == 2 * kWave)
-    rows_blk<TI, VEC, NEED_T, 2 * kWave>(a);
-  else
-    rows_blk<TI, VEC, NEED_T, kBlock>(a);
+  with_row_shape<4>(a.R, a.V, TI::kVec, [&](auto sh) {
+    using Sh = decltype(sh);
+    k_gen_rows<TI, VEC, Sh::kU, NEED_T, Sh::kBlock><<<dim3(unsigned(a.R)), Sh::kBlock, 0, a.stream>>>(
+        a.zd, a.zt, a.labels, a.V, a.sc_d, a.sc_t, a.w_eal != 0.f, a.w_wtv != 0.f || a.w_tv != 0.f || a.w_kl != 0.f,
+        a.w_kl != 0.f, a.stats);
+  });
 }
 
-template <class TI, class TG, bool VEC>
-void grad_launch(const GenArgs& a, bool need_p) {
-  constexpr int U = 4;
-  const dim3 grid(unsigned(a.R), row_splits(a.R, a.V, TI::kVec, U));
-  if (need_p)
-    k_gen_grad<TI, TG, VEC, U, true><<<grid, kBlock, 0, a.stream>>>(a.zd, a.zt, a.V, a.sc_d, a.sc_t, a.stats, a.grad);
-  else
-    k_gen_grad<TI, TG, VEC, U, false><<<grid, kBlock, 0, a.stream>>>(a.zd, a.zt, a.V, a.sc_d, a.sc_t, a.stats, a.grad);
+template <class TI, class TG, bool VEC, bool NEED_P>
+void grad_launch(const GenArgs& a) {
+  with_grad_shape(a.V, TI::kVec, [&](auto sh) {
+    constexpr int U = decltype(sh)::kU;
+    k_gen_grad<TI, TG, VEC, U, NEED_P>
+        <<<dim3(unsigned(a.R), row_splits(a.R, a.V, TI::kVec, U)), kBlock, 0, a.stream>>>(a.zd, a.zt, a.V, a.sc_d,
+                                                                                         a.sc_t, a.stats, a.grad);
+  });
 }
 
 template <class TI, bool VEC>
@@ -413,9 +404,9 @@ hipError_t launch_vec(const GenArgs& a) {
   if (hipError_t e = launch_general_loss(a); e != hipSuccess) return e;
   if (a.grad) {
     if (a.gd == DType::kBf16)
-      grad_launch<TI, GBf16, VEC>(a, need_pq);
+      need_pq ? grad_launch<TI, GBf16, VEC, true>(a) : grad_launch<TI, GBf16, VEC, false>(a);
     else
-      grad_launch<TI, GF32, VEC>(a, need_pq);
+      need_pq ? grad_launch<TI, GF32, VEC, true>(a) : grad_launch<TI, GF32, VEC, false>(a);
   }
   return hipGetLastError();
 }

@@ -207,28 +207,27 @@ __global__ __launch_bounds__(kBlock) void k_grpo_grad(const void* __restrict__ z
   }
 }
 
-template <class TI, bool VEC, int BLK>
+template <class TI, bool VEC, bool TARGET>
 void rows_launch(const GrpoArgs& a) {
-  const unsigned R = unsigned(a.R);
-  if (a.labels == nullptr)
-    k_grpo_rows<TI, VEC, 2, true, BLK><<<R, BLK, 0, a.stream>>>(a.zth, a.zrf, a.zt, a.labels, a.V, a.sc, a.rows);
-  else
-    k_grpo_rows<TI, VEC, 2, false, BLK><<<R, BLK, 0, a.stream>>>(a.zth, a.zrf, a.zt, a.labels, a.V, a.sc, a.rows);
+  with_row_shape<2>(a.R, a.V, TI::kVec, [&](auto sh) {
+    using Sh = decltype(sh);
+    k_grpo_rows<TI, VEC, Sh::kU, TARGET, Sh::kBlock>
+        <<<unsigned(a.R), Sh::kBlock, 0, a.stream>>>(a.zth, a.zrf, a.zt, a.labels, a.V, a.sc, a.rows);
+  });
 }
 
 template <class TI, class TG, bool VEC>
 void grad_launch(const GrpoArgs& a, const GroupParams& gp) {
-  constexpr int U = 4;
-  k_grpo_grad<TI, TG, VEC, U><<<dim3(unsigned(a.R), row_splits(a.R, a.V, TI::kVec, U)), kBlock, 0, a.stream>>>(
-      a.zth, a.V, a.sc, a.inv_t, a.grad_scale, gp, a.grad);
+  with_grad_shape(a.V, TI::kVec, [&](auto sh) {
+    constexpr int U = decltype(sh)::kU;
+    k_grpo_grad<TI, TG, VEC, U><<<dim3(unsigned(a.R), row_splits(a.R, a.V, TI::kVec, U)), kBlock, 0, a.stream>>>(
+        a.zth, a.V, a.sc, a.inv_t, a.grad_scale, gp, a.grad);
+  });
 }
 
 template <class TI, bool VEC>
 hipError_t launch_vec(const GrpoArgs& a) {
-  if (wide_rows(a.R, a.V))
-    rows_launch<TI, VEC, kWideBlock>(a);
-  else
-    rows_launch<TI, VEC, kBlock>(a);
+  a.labels == nullptr ? rows_launch<TI, VEC, true>(a) : rows_launch<TI, VEC, false>(a);
   GroupParams gp{};
   gp.rows = a.rows;
   gp.layout = a.layout;

@@ -9,30 +9,57 @@ namespace aal {
 
 constexpr int kRowBlock = 256;
 constexpr int kRowWaves = kRowBlock / kWave;
-constexpr int kWideBlock = 1024;
+// Threads per workgroup and vectors per thread and round of a row pass.
+template <int B, int N>
+struct RowShape {
+  static constexpr int kBlock = B;
+  static constexpr int kU = N;
+};
 
-// Workgroup size of a pass that reduces one row per workgroup.  Up to 512
-// rows of more than 8192 entries take 1024 threads each: 256-thread workgroups
-// (eight per CU) would leave wavefront slots empty below 2048 rows (EAL over 45
-// rows of 129,076, with the split gradient pass below: 284 -> 38 us).  768 rows
-// of 50,001 are slower that way (KL + TV call 144 -> 162 us: 768 workgroups of
-// 1024 threads need two rounds of the device, the second half empty).
-static inline bool wide_rows(int64_t rows, int V) { return rows <= 512 && V > 8192; }
+static inline int row_vectors(int V, int vec) { return V / vec + (V % vec != 0); }
 
-// Workgroup size of the same pass for short rows: as many wavefronts as fill
-// four vectors per thread, so that none idles through the row's reductions.
-// Against 256 threads for every short row: WTV over 2000 x 9 rows of 1,501 bf16
-// 159 -> 87 us, forward over 4000 x 7 rows of 2,045 210 -> 112 us, EAL over
-// 3000 x 12 rows of 2,000 162 -> 113 us (two waves for up to 512 vectors: WTV
-// over 3000 x 3 rows of 3,001 107 -> 80 us).
-static inline int narrow_block(int V, int vec) {
-  const int ng = V / vec + 1;
-  return ng <= kWave * 4 ? kWave : ng <= kWave * 8 ? 2 * kWave : kRowBlock;
+// The shape of a pass that reduces one row per workgroup: calls f with it.
+// A thread works through all U vectors of a round, the absent ones too, so a
+// short row takes the shape that its vectors just fill; one workgroup per CU is
+// left with few long rows, which then take as many threads as the CU holds of
+// them.  UL: U of the other rows, 4, or 2 for the GRPO pass, which reads three
+// arrays.  Kernel times against 256 x UL, us:
+//   up to 64 vectors    14,336 x 500 bf16: WTV 24.4 -> 10.9, slice partials
+//                       42.7 (ragged) -> 8.2; 512 x 500 WTV 5.1 -> 3.4
+//   up to 128           14,336 x 1,000: WTV 38 -> 16.9, 1,024 rows 6.0 -> 4.5
+//   up to 512           14,336 x 2,000: WTV 45 -> 34.2; up to 1,024 rows more
+//                       threads of fewer vectors, 512 x 2,000: 5.9 -> 4.7,
+//                       512 x 4,000: 6.7 -> 5.8
+//   few rows, over 1,024 vectors: 512 x 16,000 15.0 -> 13.6, 256 x 128,256
+//                       53.3 -> 39.3; 768 x 16,000 is slower that way (16.6 ->
+//                       17.8: three workgroups of 512 do not fit a CU), as is
+//                       the GRPO pass above 256 rows (320 x 128,256 fp32
+//                       83 -> 94)
+template <int UL, class F>
+static inline void with_row_shape(int64_t rows, int V, int vec, F&& f) {
+  const int ng = row_vectors(V, vec);
+  if (ng <= 64) return f(RowShape<64, 1>{});
+  if (ng <= 128) return f(RowShape<64, 2>{});
+  if (ng <= 512) {
+    if (rows > 1024) return f(RowShape<64, 2>{});
+    return ng <= 256 ? f(RowShape<256, 1>{}) : f(RowShape<256, 2>{});
+  }
+  if (ng > 1024 && rows <= (UL == 4 ? 512 : 256))
+    return rows <= 256 && ng > (UL == 4 ? 2048 : 4096) ? f(RowShape<1024, 2>{}) : f(RowShape<512, 2>{});
+  f(RowShape<kRowBlock, UL>{});
 }
 
-// Workgroups per row of a pass without a reduction (the gradient passes): as
-// many as bring the launch to 2048 workgroups of 256 threads, eight per CU,
-// each with at least one round of U vectors per thread.
+// U of a pass without a reduction (the gradient passes, 256 threads), called
+// with it: one vector per thread where those cover the row (WTV over 512 rows
+// of 1,003 bf16 3.8 -> 3.6 us, 14,336 rows 21.4 -> 17.1).
+template <class F>
+static inline void with_grad_shape(int V, int vec, F&& f) {
+  row_vectors(V, vec) <= kRowBlock ? f(RowShape<kRowBlock, 1>{}) : f(RowShape<kRowBlock, 4>{});
+}
+
+// Workgroups per row of such a pass: as many as bring the launch to 2048
+// workgroups of 256 threads, eight per CU, each with at least one round of U
+// vectors per thread.
 static inline unsigned row_splits(int64_t rows, int V, int vec, int U) {
   const int64_t rounds = (int64_t(V) / vec + kRowBlock * U - 1) / (kRowBlock * U);
   const int64_t want = (2048 + rows - 1) / rows;

@@ -252,10 +252,14 @@ hipError_t launch_rows(const SimArgs& a) {
   return hipGetLastError();
 }
 
+// Up to 512 rows of more than 8192 entries take 1024 threads each: workgroups of
+// 256 would leave wavefront slots empty (512 rows of 128,256 bf16 48.6 -> 44.2
+// us, of 9,003 12.5 -> 11.3, 48 rows of 128,256 40 -> 20.5).  768 rows of 9,000
+// are slower that way (11.4 -> 13.9).
 template <class TI, bool VEC>
 hipError_t launch_rows_v(const SimArgs& a) {
-  return wide_rows(int64_t(a.P) * a.G * a.K, a.V) ? launch_rows<TI, VEC, 2, kWideBlock>(a)
-                                                  : launch_rows<TI, VEC, 2, kBlock>(a);
+  const bool wide = int64_t(a.P) * a.G * a.K <= 512 && a.V > 8192;
+  return wide ? launch_rows<TI, VEC, 2, 1024>(a) : launch_rows<TI, VEC, 2, kBlock>(a);
 }
 
 template <class TI>

@@ -214,30 +214,23 @@ __global__ __launch_bounds__(kBlock) void k_grad(const void* __restrict__ zd, co
   }
 }
 
-template <class TI, int MODE, bool VEC, int BLK>
-void stats_launch(const LossArgs& a) {
-  k_row_stats<TI, MODE, VEC, 4, BLK><<<dim3(unsigned(a.N * a.K)), BLK, 0, a.stream>>>(a.zd, a.zt, a.V, a.sc_d, a.sc_t,
-                                                                                     a.ws.stats);
-}
-
 template <class TI, class TG, int MODE, bool VEC>
 void grad_launch(const LossArgs& a) {
-  constexpr int U = 4;
   const int64_t rows = a.N * a.K;
-  k_grad<TI, TG, MODE, VEC, U><<<dim3(unsigned(rows), row_splits(rows, a.V, TI::kVec, U)), kBlock, 0, a.stream>>>(
-      a.zd, a.zt, a.V, a.sc_d, a.sc_t, a.ws.stats, a.grad);
+  with_grad_shape(a.V, TI::kVec, [&](auto sh) {
+    constexpr int U = decltype(sh)::kU;
+    k_grad<TI, TG, MODE, VEC, U><<<dim3(unsigned(rows), row_splits(rows, a.V, TI::kVec, U)), kBlock, 0, a.stream>>>(
+        a.zd, a.zt, a.V, a.sc_d, a.sc_t, a.ws.stats, a.grad);
+  });
 }
 
 template <class TI, int MODE, bool VEC>
 hipError_t launch_vec(const LossArgs& a) {
-  if (wide_rows(a.N * a.K, a.V))
-    stats_launch<TI, MODE, VEC, kWideBlock>(a);
-  else if (const int blk = narrow_block(a.V, TI::kVec); blk == kWave)
-    stats_launch<TI, MODE, VEC, kWave>(a);
-  else if (blk == 2 * kWave)
-    stats_launch<TI, MODE, VEC, 2 * kWave>(a);
-  else
-    stats_launch<TI, MODE, VEC, kBlock>(a);
+  with_row_shape<4>(a.N * a.K, a.V, TI::kVec, [&](auto sh) {
+    using Sh = decltype(sh);
+    k_row_stats<TI, MODE, VEC, Sh::kU, Sh::kBlock><<<dim3(unsigned(a.N * a.K)), Sh::kBlock, 0, a.stream>>>(
+        a.zd, a.zt, a.V, a.sc_d, a.sc_t, a.ws.stats);
+  });
   const unsigned wblocks = unsigned((a.N + kBlock - 1) / kBlock);
   k_window_scan<<<wblocks, kBlock, 0, a.stream>>>(a.ws.stats, a.N, a.K, MODE, a.inv_t_d, a.grad_scale, a.window_e,
                                                   a.accept, a.xstar);

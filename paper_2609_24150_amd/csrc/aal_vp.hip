@@ -381,20 +381,18 @@ __global__ __launch_bounds__(kBlock) void k_vp_grad(const void* __restrict__ zd,
   }
 }
 
-template <class TI, int MODE, bool LAB, bool VEC, int BLK>
-void partials_blk(const VpSlice& s, aal_vp_part_t* parts) {
-  k_vp_partials<TI, MODE, VEC, 4, LAB, BLK><<<row_grid(s.rows), BLK, 0, s.stream>>>(
-      s.zd, s.zt, s.labels, s.rows, s.vs, s.v0, s.vtot, s.scd, s.sct, parts);
+template <class TI, int MODE, bool LAB, bool VEC>
+void partials_vec(const VpSlice& s, aal_vp_part_t* parts) {
+  with_row_shape<4>(s.rows, s.vs, TI::kVec, [&](auto sh) {
+    using Sh = decltype(sh);
+    k_vp_partials<TI, MODE, VEC, Sh::kU, LAB, Sh::kBlock><<<row_grid(s.rows), Sh::kBlock, 0, s.stream>>>(
+        s.zd, s.zt, s.labels, s.rows, s.vs, s.v0, s.vtot, s.scd, s.sct, parts);
+  });
 }
 
 template <class TI, int MODE, bool LAB>
 void partials_lab(const VpSlice& s, aal_vp_part_t* parts) {
-  const bool vec = s.vs % TI::kVec == 0;
-  if (wide_rows(s.rows, s.vs))
-    vec ? partials_blk<TI, MODE, LAB, true, kWideBlock>(s, parts)
-        : partials_blk<TI, MODE, LAB, false, kWideBlock>(s, parts);
-  else
-    vec ? partials_blk<TI, MODE, LAB, true, kBlock>(s, parts) : partials_blk<TI, MODE, LAB, false, kBlock>(s, parts);
+  s.vs % TI::kVec == 0 ? partials_vec<TI, MODE, LAB, true>(s, parts) : partials_vec<TI, MODE, LAB, false>(s, parts);
 }
 
 template <class TI, int MODE>
@@ -408,31 +406,33 @@ void partials_typed(const VpSlice& s, aal_vp_part_t* parts) {
   partials_lab<TI, MODE, false>(s, parts);
 }
 
-template <class TI, bool VEC, int BLK>
-void accept_blk(const VpSlice& s, const aal_vp_row_t* row, aal_vp_acc_t* acc) {
-  k_vp_accept<TI, VEC, 4, BLK>
-      <<<row_grid(s.rows), BLK, 0, s.stream>>>(s.zd, s.zt, s.rows, s.vs, s.scd, s.sct, row, acc);
+template <class TI, bool VEC>
+void accept_vec(const VpSlice& s, const aal_vp_row_t* row, aal_vp_acc_t* acc) {
+  with_row_shape<4>(s.rows, s.vs, TI::kVec, [&](auto sh) {
+    using Sh = decltype(sh);
+    k_vp_accept<TI, VEC, Sh::kU, Sh::kBlock>
+        <<<row_grid(s.rows), Sh::kBlock, 0, s.stream>>>(s.zd, s.zt, s.rows, s.vs, s.scd, s.sct, row, acc);
+  });
 }
 
 template <class TI>
 void accept_typed(const VpSlice& s, const aal_vp_row_t* row, aal_vp_acc_t* acc) {
-  const bool vec = s.vs % TI::kVec == 0;
-  if (wide_rows(s.rows, s.vs))
-    vec ? accept_blk<TI, true, kWideBlock>(s, row, acc) : accept_blk<TI, false, kWideBlock>(s, row, acc);
-  else
-    vec ? accept_blk<TI, true, kBlock>(s, row, acc) : accept_blk<TI, false, kBlock>(s, row, acc);
+  s.vs % TI::kVec == 0 ? accept_vec<TI, true>(s, row, acc) : accept_vec<TI, false>(s, row, acc);
+}
+
+template <class TI, class TG, int MODE, bool VEC>
+void grad_vec(const VpSlice& s, const aal_vp_row_t* row, void* grad) {
+  with_grad_shape(s.vs, TI::kVec, [&](auto sh) {
+    constexpr int U = decltype(sh)::kU;
+    k_vp_grad<TI, TG, MODE, VEC, U>
+        <<<dim3(row_grid(s.rows), row_splits(s.rows, s.vs, TI::kVec, U)), kBlock, 0, s.stream>>>(
+            s.zd, s.zt, s.rows, s.vs, s.v0, s.scd, s.sct, row, grad);
+  });
 }
 
 template <class TI, class TG, int MODE>
 void grad_typed(const VpSlice& s, const aal_vp_row_t* row, void* grad) {
-  constexpr int U = 4;
-  const dim3 grid(row_grid(s.rows), row_splits(s.rows, s.vs, TI::kVec, U));
-  if (s.vs % TI::kVec == 0)
-    k_vp_grad<TI, TG, MODE, true, U>
-        <<<grid, kBlock, 0, s.stream>>>(s.zd, s.zt, s.rows, s.vs, s.v0, s.scd, s.sct, row, grad);
-  else
-    k_vp_grad<TI, TG, MODE, false, U>
-        <<<grid, kBlock, 0, s.stream>>>(s.zd, s.zt, s.rows, s.vs, s.v0, s.scd, s.sct, row, grad);
+  s.vs % TI::kVec == 0 ? grad_vec<TI, TG, MODE, true>(s, row, grad) : grad_vec<TI, TG, MODE, false>(s, row, grad);
 }
 
 template <class TG>

@@ -1,12 +1,11 @@
-"""Rows that start and end inside 16-byte vectors, and the wide (1024-thread)
-and split launches of the workgroup-per-row kernels, against the fp64 oracle
-with the tolerances of the entry points' own parity tests.
+"""Rows that start and end inside 16-byte vectors, and every shape that the
+workgroup-per-row kernels are launched in, against the fp64 oracle with the
+tolerances of the entry points' own parity tests.
 
 The sizes put a row's edges everywhere they can fall: rows shorter than a
 vector, rows whose first and last vectors are the same, a last row that ends
-the allocation inside a vector, more than 8192 entries (wide workgroups) with
-few rows, 513 rows (the first count that is not wide), and the row lengths at
-which a row pass goes from one wavefront to two and to four."""
+the allocation inside a vector; and rows and lengths on both sides of each
+limit at which a pass takes other workgroups."""
 import pytest
 import torch
 
@@ -21,7 +20,10 @@ BF16, F32 = torch.bfloat16, torch.float32
 SHAPES = [(3, 3, 5), (9, 2, 3), (17, 1, 2), (8193, 3, 2), (8200, 2, 2), (20003, 5, 1), (8197, 1, 513),
           (1023, 2, 3), (1024, 2, 3), (2047, 2, 3), (2048, 2, 3), (4095, 2, 3), (4096, 2, 3),
           # arrays that end 1, 3 and 4 elements into a vector (and 2, 5, 6, 7 above), arrays shorter than one
-          (5, 1, 5), (11, 3, 3), (3, 1, 4), (3, 1, 2), (1, 1, 3)]  # V, K, N
+          (5, 1, 5), (11, 3, 3), (3, 1, 4), (3, 1, 2), (1, 1, 3),
+          # either side of the row shapes' limits in vectors (64, 128, 256, 512, 1024, 2048, 4096) and rows
+          (511, 3, 3), (513, 2, 3), (2049, 5, 210), (4095, 5, 210), (8201, 1, 257), (16400, 1, 257),
+          (32777, 1, 4)]  # V, K, N
 
 
 @pytest.fixture(scope="module")
