@@ -31,9 +31,9 @@ constexpr float kLn2 = 0.693147180559945309417f;
 
 template <class TI, bool VEC, int U, bool NEED_T, int BLK>
 __global__ __launch_bounds__(BLK) void k_gen_rows(const void* __restrict__ zd, const void* __restrict__ zt,
-                                                     const int32_t* __restrict__ labels, int V, float scd,
-                                                     float sct, int want_eal, int want_pq, int want_kl,
-                                                     GenStats* __restrict__ stats) {
+                                                  const int32_t* __restrict__ labels, int64_t rows, int V,
+                                                  float scd, float sct, int want_eal, int want_pq, int want_kl,
+                                                  GenStats* __restrict__ stats) {
   using Rv = RowVecs<TI, VEC>;
   constexpr int E = Rv::E;
   __shared__ LseState sh_lse[BLK / kWave];
@@ -41,7 +41,7 @@ __global__ __launch_bounds__(BLK) void k_gen_rows(const void* __restrict__ zd, c
   __shared__ int sh_i[BLK / kWave];
 
   const int64_t row = blockIdx.x;
-  const Rv rv(row, gridDim.x, V);
+  const Rv rv(row, rows, V);
   const int64_t e0 = row * int64_t(V);
   const bool argmax = NEED_T && want_eal && labels == nullptr;
 
@@ -309,16 +309,16 @@ __global__ void k_gen_loss(const double* __restrict__ parts, int64_t R, int64_t 
 }
 
 template <class TI, class TG, bool VEC, int U, bool NEED_P>
-__global__ __launch_bounds__(kBlock) void k_gen_grad(const void* __restrict__ zd, const void* __restrict__ zt, int V,
-                                                     float scd, float sct, const GenStats* __restrict__ stats,
-                                                     void* __restrict__ grad) {
+__global__ __launch_bounds__(kBlock) void k_gen_grad(const void* __restrict__ zd, const void* __restrict__ zt,
+                                                     int64_t rows, int splits, int V, float scd, float sct,
+                                                     const GenStats* __restrict__ stats, void* __restrict__ grad) {
   using Rv = RowVecs<TI, VEC>;
   constexpr int E = Rv::E;
   constexpr int NT = NEED_P ? 2 : 1;
   const int64_t row = blockIdx.x;
-  const Rv rv(row, gridDim.x, V);
+  const Rv rv(row, rows, V);
   const GenStats s = stats[row];
-  for (int base = blockIdx.y * kBlock * U + threadIdx.x; base < rv.ng; base += gridDim.y * kBlock * U) {
+  for (int base = blockIdx.y * kBlock * U + threadIdx.x; base < rv.ng; base += splits * kBlock * U) {
     u32x4 w[NT][U];
     if constexpr (NEED_P)
       rv.load({zd, zt}, base, kBlock, w);
@@ -356,7 +356,7 @@ void rows_launch(const GenArgs& a) {
   with_row_shape<4>(a.R, a.V, TI::kVec, [&](auto sh) {
     using Sh = decltype(sh);
     k_gen_rows<TI, VEC, Sh::kU, NEED_T, Sh::kBlock><<<dim3(unsigned(a.R)), Sh::kBlock, 0, a.stream>>>(
-        a.zd, a.zt, a.labels, a.V, a.sc_d, a.sc_t, a.w_eal != 0.f, a.w_wtv != 0.f || a.w_tv != 0.f || a.w_kl != 0.f,
+        a.zd, a.zt, a.labels, a.R, a.V, a.sc_d, a.sc_t, a.w_eal != 0.f, a.w_wtv != 0.f || a.w_tv != 0.f || a.w_kl != 0.f,
         a.w_kl != 0.f, a.stats);
   });
 }
@@ -365,9 +365,9 @@ template <class TI, class TG, bool VEC, bool NEED_P>
 void grad_launch(const GenArgs& a) {
   with_grad_shape(a.V, TI::kVec, [&](auto sh) {
     constexpr int U = decltype(sh)::kU;
-    k_gen_grad<TI, TG, VEC, U, NEED_P>
-        <<<dim3(unsigned(a.R), row_splits(a.R, a.V, TI::kVec, U)), kBlock, 0, a.stream>>>(a.zd, a.zt, a.V, a.sc_d,
-                                                                                         a.sc_t, a.stats, a.grad);
+    const unsigned splits = row_splits(a.R, a.V, TI::kVec, U);
+    k_gen_grad<TI, TG, VEC, U, NEED_P><<<dim3(unsigned(a.R), splits), kBlock, 0, a.stream>>>(
+        a.zd, a.zt, a.R, int(splits), a.V, a.sc_d, a.sc_t, a.stats, a.grad);
   });
 }
 

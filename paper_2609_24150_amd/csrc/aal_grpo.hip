@@ -31,8 +31,8 @@ constexpr float kLn2 = 0.693147180559945309417f;
 
 template <class TI, bool VEC, int U, bool TARGET, int BLK>
 __global__ __launch_bounds__(BLK) void k_grpo_rows(const void* __restrict__ zth, const void* __restrict__ zrf,
-                                                      const void* __restrict__ zt, const int32_t* __restrict__ labels,
-                                                      int V, float sc, GrpoRow* __restrict__ rows) {
+                                                   const void* __restrict__ zt, const int32_t* __restrict__ labels,
+                                                   int64_t nrows, int V, float sc, GrpoRow* __restrict__ rows) {
   using Rv = RowVecs<TI, VEC>;
   constexpr int E = Rv::E;
   __shared__ LseState sh_lse[BLK / kWave];
@@ -40,7 +40,7 @@ __global__ __launch_bounds__(BLK) void k_grpo_rows(const void* __restrict__ zth,
   __shared__ int sh_i[BLK / kWave];
 
   const int64_t row = blockIdx.x;
-  const Rv rv(row, gridDim.x, V);
+  const Rv rv(row, nrows, V);
   const int64_t e0 = row * int64_t(V);
 
   LseState sth = lse_init(), srf = lse_init();
@@ -158,9 +158,9 @@ __global__ __launch_bounds__(kBlock) void k_grpo_loss(const float* __restrict__ 
 }
 
 template <class TI, class TG, bool VEC, int U>
-__global__ __launch_bounds__(kBlock) void k_grpo_grad(const void* __restrict__ zth, int V, float sc, float inv_t,
-                                                      const float* __restrict__ grad_scale, GroupParams p,
-                                                      void* __restrict__ grad) {
+__global__ __launch_bounds__(kBlock) void k_grpo_grad(const void* __restrict__ zth, int64_t nrows, int splits, int V,
+                                                      float sc, float inv_t, const float* __restrict__ grad_scale,
+                                                      GroupParams p, void* __restrict__ grad) {
   using Rv = RowVecs<TI, VEC>;
   constexpr int E = Rv::E;
   __shared__ float sh_c;
@@ -187,8 +187,8 @@ __global__ __launch_bounds__(kBlock) void k_grpo_grad(const void* __restrict__ z
   }
   __syncthreads();
   const float c = sh_c;
-  const Rv rv(row, gridDim.x, V);
-  for (int base = blockIdx.y * kBlock * U + threadIdx.x; base < rv.ng; base += gridDim.y * kBlock * U) {
+  const Rv rv(row, nrows, V);
+  for (int base = blockIdx.y * kBlock * U + threadIdx.x; base < rv.ng; base += splits * kBlock * U) {
     u32x4 w[1][U];
     rv.load({zth}, base, kBlock, w);
 #pragma unroll
@@ -212,7 +212,7 @@ void rows_launch(const GrpoArgs& a) {
   with_row_shape<2>(a.R, a.V, TI::kVec, [&](auto sh) {
     using Sh = decltype(sh);
     k_grpo_rows<TI, VEC, Sh::kU, TARGET, Sh::kBlock>
-        <<<unsigned(a.R), Sh::kBlock, 0, a.stream>>>(a.zth, a.zrf, a.zt, a.labels, a.V, a.sc, a.rows);
+        <<<unsigned(a.R), Sh::kBlock, 0, a.stream>>>(a.zth, a.zrf, a.zt, a.labels, a.R, a.V, a.sc, a.rows);
   });
 }
 
@@ -220,8 +220,9 @@ template <class TI, class TG, bool VEC>
 void grad_launch(const GrpoArgs& a, const GroupParams& gp) {
   with_grad_shape(a.V, TI::kVec, [&](auto sh) {
     constexpr int U = decltype(sh)::kU;
-    k_grpo_grad<TI, TG, VEC, U><<<dim3(unsigned(a.R), row_splits(a.R, a.V, TI::kVec, U)), kBlock, 0, a.stream>>>(
-        a.zth, a.V, a.sc, a.inv_t, a.grad_scale, gp, a.grad);
+    const unsigned splits = row_splits(a.R, a.V, TI::kVec, U);
+    k_grpo_grad<TI, TG, VEC, U><<<dim3(unsigned(a.R), splits), kBlock, 0, a.stream>>>(
+        a.zth, a.R, int(splits), a.V, a.sc, a.inv_t, a.grad_scale, gp, a.grad);
   });
 }
 

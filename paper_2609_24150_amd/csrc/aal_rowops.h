@@ -93,6 +93,9 @@ struct RowVecs {
   int head;    // elements of the first vector before the row
   int V;
 
+  // rows (and the splits of a gradient pass) reach a kernel as arguments:
+  // gridDim would come with the runtime's hidden ones, 1.3 us more to enqueue a
+  // WTV call (13.9 against 15.2 without Python).
   __device__ __forceinline__ RowVecs(int64_t row, int64_t rows, int v) : V(v) {
     if constexpr (ALIGNED) {
       nload = nfull = ng = v / E;

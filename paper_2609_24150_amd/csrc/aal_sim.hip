@@ -31,10 +31,10 @@ static __device__ __forceinline__ double tile_mass(const float2* ts, int t, floa
 }
 
 template <class TI, bool VEC, int U, int BLK>
-__global__ __launch_bounds__(BLK) void k_sim_rows(const void* __restrict__ zd, const void* __restrict__ zt, int V,
-                                                     float sc, const float* __restrict__ u1,
-                                                     const float* __restrict__ u2, int32_t* __restrict__ token,
-                                                     int32_t* __restrict__ accept) {
+__global__ __launch_bounds__(BLK) void k_sim_rows(const void* __restrict__ zd, const void* __restrict__ zt,
+                                                  int64_t rows, int V, float sc, const float* __restrict__ u1,
+                                                  const float* __restrict__ u2, int32_t* __restrict__ token,
+                                                  int32_t* __restrict__ accept) {
   using Rv = RowVecs<TI, VEC>;
   constexpr int E = Rv::E;
   constexpr int TG = kWave * U;  // element groups per tile
@@ -45,7 +45,7 @@ __global__ __launch_bounds__(BLK) void k_sim_rows(const void* __restrict__ zd, c
   __shared__ float sh_msc, sh_l2s;
 
   const int64_t row = blockIdx.x;
-  const Rv rv(row, gridDim.x, V);
+  const Rv rv(row, rows, V);
   const int ntiles = (rv.ng + TG - 1) / TG;
   const int64_t e0 = row * int64_t(V);
   const int w = threadIdx.x / kWave;
@@ -247,7 +247,7 @@ hipError_t launch_rows(const SimArgs& a) {
   const int ntiles = (ng + kWave * U - 1) / (kWave * U);
   const size_t lds = size_t(ntiles) * sizeof(float2);
   const int64_t rows = int64_t(a.P) * a.G * a.K;
-  k_sim_rows<TI, VEC, U, BLK><<<dim3(unsigned(rows)), BLK, lds, a.stream>>>(a.zd, a.zt, a.V, a.sc, a.u1, a.u2,
+  k_sim_rows<TI, VEC, U, BLK><<<dim3(unsigned(rows)), BLK, lds, a.stream>>>(a.zd, a.zt, rows, a.V, a.sc, a.u1, a.u2,
                                                                           a.token, a.accept);
   return hipGetLastError();
 }

@@ -27,8 +27,8 @@ constexpr int kWaves = kRowWaves;
 
 template <class TI, int MODE, bool VEC, int U, int BLK>
 __global__ __launch_bounds__(BLK) void k_row_stats(const void* __restrict__ zd, const void* __restrict__ zt,
-                                                      int V, float scd, float sct,
-                                                      RowStats* __restrict__ stats) {
+                                                   int64_t rows, int V, float scd, float sct,
+                                                   RowStats* __restrict__ stats) {
   using Rv = RowVecs<TI, VEC>;
   constexpr int E = Rv::E;
   __shared__ LseState sh_lse[BLK / kWave];
@@ -36,7 +36,7 @@ __global__ __launch_bounds__(BLK) void k_row_stats(const void* __restrict__ zd, 
   __shared__ int sh_i[BLK / kWave];
 
   const int64_t row = blockIdx.x;
-  const Rv rv(row, gridDim.x, V);
+  const Rv rv(row, rows, V);
   const int64_t e0 = row * int64_t(V);
 
   LseState sd = lse_init(), st = lse_init();
@@ -167,19 +167,19 @@ __global__ __launch_bounds__(kBlock) void k_loss(const float* __restrict__ windo
 }
 
 template <class TI, class TG, int MODE, bool VEC, int U>
-__global__ __launch_bounds__(kBlock) void k_grad(const void* __restrict__ zd, const void* __restrict__ zt, int V,
-                                                 float scd, float sct, const RowStats* __restrict__ stats,
-                                                 void* __restrict__ grad) {
+__global__ __launch_bounds__(kBlock) void k_grad(const void* __restrict__ zd, const void* __restrict__ zt, int64_t rows,
+                                                 int splits, int V, float scd, float sct,
+                                                 const RowStats* __restrict__ stats, void* __restrict__ grad) {
   using Rv = RowVecs<TI, VEC>;
   constexpr int E = Rv::E;
   constexpr int NT = MODE == int(Mode::kEal) ? 1 : 2;  // logit arrays read
   const int64_t row = blockIdx.x;
-  const Rv rv(row, gridDim.x, V);
+  const Rv rv(row, rows, V);
   const RowStats s = stats[row];
   const float c = s.coef;
   const float cA = c * (1.f - s.qlt);  // WTV, entries with q < p
   const float cB = -c * s.qlt;         // WTV, the others
-  for (int base = blockIdx.y * kBlock * U + threadIdx.x; base < rv.ng; base += gridDim.y * kBlock * U) {
+  for (int base = blockIdx.y * kBlock * U + threadIdx.x; base < rv.ng; base += splits * kBlock * U) {
     u32x4 w[NT][U];  // loaded together: a launch of few wavefronts waits once per round
     if constexpr (NT == 2)
       rv.load({zd, zt}, base, kBlock, w);
@@ -219,17 +219,19 @@ void grad_launch(const LossArgs& a) {
   const int64_t rows = a.N * a.K;
   with_grad_shape(a.V, TI::kVec, [&](auto sh) {
     constexpr int U = decltype(sh)::kU;
-    k_grad<TI, TG, MODE, VEC, U><<<dim3(unsigned(rows), row_splits(rows, a.V, TI::kVec, U)), kBlock, 0, a.stream>>>(
-        a.zd, a.zt, a.V, a.sc_d, a.sc_t, a.ws.stats, a.grad);
+    const unsigned splits = row_splits(rows, a.V, TI::kVec, U);
+    k_grad<TI, TG, MODE, VEC, U><<<dim3(unsigned(rows), splits), kBlock, 0, a.stream>>>(
+        a.zd, a.zt, rows, int(splits), a.V, a.sc_d, a.sc_t, a.ws.stats, a.grad);
   });
 }
 
 template <class TI, int MODE, bool VEC>
 hipError_t launch_vec(const LossArgs& a) {
-  with_row_shape<4>(a.N * a.K, a.V, TI::kVec, [&](auto sh) {
+  const int64_t rows = a.N * a.K;
+  with_row_shape<4>(rows, a.V, TI::kVec, [&](auto sh) {
     using Sh = decltype(sh);
-    k_row_stats<TI, MODE, VEC, Sh::kU, Sh::kBlock><<<dim3(unsigned(a.N * a.K)), Sh::kBlock, 0, a.stream>>>(
-        a.zd, a.zt, a.V, a.sc_d, a.sc_t, a.ws.stats);
+    k_row_stats<TI, MODE, VEC, Sh::kU, Sh::kBlock><<<dim3(unsigned(rows)), Sh::kBlock, 0, a.stream>>>(
+        a.zd, a.zt, rows, a.V, a.sc_d, a.sc_t, a.ws.stats);
   });
   const unsigned wblocks = unsigned((a.N + kBlock - 1) / kBlock);
   k_window_scan<<<wblocks, kBlock, 0, a.stream>>>(a.ws.stats, a.N, a.K, MODE, a.inv_t_d, a.grad_scale, a.window_e,
