@@ -24,25 +24,23 @@ static inline int row_vectors(int V, int vec) { return V / vec + (V % vec != 0);
 // left with few long rows, which then take as many threads as the CU holds of
 // them.  UL: U of the other rows, 4, or 2 for the GRPO pass, which reads three
 // arrays.  Kernel times against 256 x UL, us:
-//   up to 64 vectors    14,336 x 500 bf16: WTV 24.4 -> 10.9, slice partials
-//                       42.7 (ragged) -> 8.2; 512 x 500 WTV 5.1 -> 3.4
-//   up to 128           14,336 x 1,000: WTV 38 -> 16.9, 1,024 rows 6.0 -> 4.5
-//   up to 512           14,336 x 2,000: WTV 45 -> 34.2; up to 1,024 rows more
-//                       threads of fewer vectors, 512 x 2,000: 5.9 -> 4.7,
-//                       512 x 4,000: 6.7 -> 5.8
+//   up to 64 vectors    14,336 x 500 bf16: WTV 51.2 -> 10.9, slice partials
+//                       42.7 (ragged) -> 8.2; 512 x 500 WTV 5.0 -> 3.4
+//   up to 512           WTV 14,336 x 1,000 66.7 -> 16.9, x 2,000 97.3 -> 34.2; up
+//                       to 1,024 rows more threads of fewer vectors: 768 x 1,003
+//                       10.9 -> 5.5 (6.5 with 64 x 2), 512 x 2,000 6.9 -> 4.7,
+//                       512 x 4,000 7.3 -> 5.8
 //   few rows, over 1,024 vectors: 512 x 16,000 15.0 -> 13.6, 256 x 128,256
 //                       53.3 -> 39.3; 768 x 16,000 is slower that way (16.6 ->
-//                       17.8: three workgroups of 512 do not fit a CU), as is
-//                       the GRPO pass above 256 rows (320 x 128,256 fp32
-//                       83 -> 94)
+//                       17.8), as is the GRPO pass above 256 rows (320 x 128,256
+//                       fp32 83 -> 94)
 template <int UL, class F>
 static inline void with_row_shape(int64_t rows, int V, int vec, F&& f) {
   const int ng = row_vectors(V, vec);
   if (ng <= 64) return f(RowShape<64, 1>{});
-  if (ng <= 128) return f(RowShape<64, 2>{});
   if (ng <= 512) {
     if (rows > 1024) return f(RowShape<64, 2>{});
-    return ng <= 256 ? f(RowShape<256, 1>{}) : f(RowShape<256, 2>{});
+    return ng <= 128 ? f(RowShape<128, 1>{}) : ng <= 256 ? f(RowShape<256, 1>{}) : f(RowShape<256, 2>{});
   }
   if (ng > 1024 && rows <= (UL == 4 ? 512 : 256))
     return rows <= 256 && ng > (UL == 4 ? 2048 : 4096) ? f(RowShape<1024, 2>{}) : f(RowShape<512, 2>{});
