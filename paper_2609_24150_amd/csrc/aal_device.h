@@ -56,15 +56,6 @@ typedef float f32x4 __attribute__((ext_vector_type(4)));
 
 static __device__ __forceinline__ uint4 to_uint4(u32x4 v) { return make_uint4(v.x, v.y, v.z, v.w); }
 
-// 16-byte vector load of vector index `vi` (in units of 16 bytes).
-static __device__ __forceinline__ uint4 ldvec(const void* base, int64_t vi) {
-  return to_uint4(static_cast<const u32x4*>(base)[vi]);
-}
-// Streaming variant: data read exactly once, no reuse expected.
-static __device__ __forceinline__ uint4 ldvec_nt(const void* base, int64_t vi) {
-  return to_uint4(__builtin_nontemporal_load(static_cast<const u32x4*>(base) + vi));
-}
-
 // Gradient element types.  bf16 stores round to nearest even (one
 // v_cvt_pk_bf16_f32 per pair).
 typedef float f32x2 __attribute__((ext_vector_type(2)));
