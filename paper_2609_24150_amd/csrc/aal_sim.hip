@@ -53,11 +53,11 @@ __global__ __launch_bounds__(BLK) void k_sim_rows(const void* __restrict__ zd, c
 
   LseState st = lse_init();
   for (int t = w; t < ntiles; t += BLK / kWave) {
-    u32x4 w[2][U];
+    u32x4 z[2][U];
     float xd[U][E], xt[U][E];
-    rv.load({zd, zt}, t * TG + lane, kWave, w);
-    rv.unpack(w[0], xd);
-    rv.unpack(w[1], xt);
+    rv.load({zd, zt}, t * TG + lane, kWave, z);
+    rv.unpack(z[0], xd);
+    rv.unpack(z[1], xt);
     float lm = kNegInf;
 #pragma unroll
     for (int u = 0; u < U; ++u)
