@@ -74,10 +74,10 @@ static inline unsigned row_splits(int64_t rows, int V, int vec, int U) {
 // past the allocation: in its place the array's last 16 bytes are loaded, by
 // the same instruction, and moved to where they belong (an array of less than
 // 16 bytes is read element by element).  The stores at a row's edges go
-// element by element.  Against element-by-element accesses of
-// the whole row: the simulation over 447,252 rows of 2,587 bf16 logits 4.12 ->
-// 1.51 ms, the KL + TV passes over 768 rows of 50,001 145 + 77 -> 83 + 47 us,
-// the WTV passes over 1792 rows of 32,001 117 + 75 -> 94 + 70 us.
+// element by element.  Against element-by-element accesses of the whole row:
+// the simulation over 447,252 rows of 2,587 bf16 logits 4.12 -> 1.51 ms, the
+// KL + TV passes over 768 rows of 50,001 145 + 77 -> 72 + 46 us, the WTV passes
+// over 1792 rows of 32,001 117 + 75 -> 78 + 68 us.
 typedef u32x4 u32x4_any __attribute__((aligned(2)));  // a vector at any element
 
 template <class TI, bool ALIGNED>
