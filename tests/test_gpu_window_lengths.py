@@ -104,3 +104,47 @@ def test_no_waits_between_workgroups(A, K, monkeypatch):
         r = call(grad=True, flags=0)
         torch.cuda.synchronize()
         assert math.isfinite(r["loss"].item()), name
+
+
+@pytest.mark.parametrize("K", [9, 12, 15])
+def test_unflagged_calls_on_two_streams(A, K):
+    """Two device-filling calls at once, without AAL_FLAG_COOPERATIVE: each gives a lone call's bits."""
+    dev = torch.device("cuda:0")
+    calls = [c for name, c in _calls(A, K, dev).items() if name in ("wtv", "eal", "wtv fp32")]
+    refs = [c() for c in calls]
+    torch.cuda.synchronize()
+    streams = [torch.cuda.Stream(dev), torch.cuda.Stream(dev)]
+    outs = []
+    for _ in range(3):
+        for call, ref in zip(calls, refs):
+            for s in streams:
+                with torch.cuda.stream(s):
+                    outs.append((call(stream=s), ref))
+    torch.cuda.synchronize()
+    for r, ref in outs:
+        for k, v in ref.items():
+            if v is not None:
+                assert torch.equal(r[k].view(torch.uint8), v.view(torch.uint8)), k
+
+
+@pytest.mark.parametrize("K", [9, 12, 15])
+def test_flagged_calls_can_be_captured(A, K):
+    """AAL_FLAG_COOPERATIVE needs no cooperative launch at these lengths, so the call goes into a graph;
+    three replays with eager work between them."""
+    calls = _calls(A, K, torch.device("cuda:0"))
+    for name in ("wtv", "eal"):
+        ref = calls[name](flags=A.AAL_FLAG_COOPERATIVE)
+        torch.cuda.synchronize()
+        graph = torch.cuda.CUDAGraph()
+        with torch.cuda.graph(graph):
+            r = calls[name](flags=A.AAL_FLAG_COOPERATIVE)
+        for _ in range(3):
+            for v in r.values():
+                if v is not None:
+                    v.zero_()
+            calls[name]()
+            graph.replay()
+            torch.cuda.synchronize()
+            for k, v in ref.items():
+                if v is not None:
+                    assert torch.equal(r[k].view(torch.uint8), v.view(torch.uint8)), (name, k)
